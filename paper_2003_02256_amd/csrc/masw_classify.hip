@@ -36,15 +36,35 @@
 // exactly at the modes; the positive factors dropped by the
 // orthonormalisation leave its sign and zeros unchanged.
 //
-// Work split.  One wavefront per wavelength, four per workgroup.  Lane l
-// evaluates F at point l
-// of 64 equally spaced points of the bracket: a different sign at the two
-// ends is a mode, and the first lane whose sign differs from the lower end's
-// gives the next bracket, 63 times narrower (multisection), until it is no
-// wider than 1e-12 c_test[idx].  Control flow is uniform across the wavefront
-// (ballots and shuffles); each lane's layer loop runs its own step count.
+// Work split.  Eight lanes per wavelength, eight wavelengths per wavefront,
+// four wavefronts per workgroup.  The eight lanes evaluate F at eight points
+// at once: first at both ends of the bracket and six equally spaced points
+// between them (a different sign at the two ends is a mode), then at points
+// around the root that the degree-7 polynomial through those values gives,
+// two of them 0.9 tol apart, tol = 1e-12 c_test[idx], and six on a widening
+// ladder on both sides.  The first point whose sign differs from the lower
+// end's gives the next bracket, so a root estimate good to half of tol ends
+// the search in two rounds, 16 evaluations, and an estimate off by a rung or
+// two narrows the bracket to that rung, with linear interpolation for the
+// next round.  A root beyond the ladder, or not reached in kMaxRounds (a grid
+// step of many m/s, several roots in one step), is deferred to a second
+// launch, in which a whole wavefront multisects it with 64 points a round.
+// For the interpolation F is the analytic dispersion function: the
+// orthonormalisations' divisors are multiplied back in, and each layer is cut
+// into the same number of steps at every point of a bracket (the larger of
+// the two ends' needs).
+// Bound by the vector ALU (67% busy; the rest is the end of the launch and
+// the latency of three wavefronts a SIMD): what counts is the evaluations
+// per pick.  141,745 picks of 512 models (3 to 30 layers, grid 0.05 m/s): 16.0
+// evaluations a pick and 0.75 ms, against 320 and 8.9 ms with 64 lanes a pick
+// multisecting 63-fold.  Without the divisors multiplied back, 0.4% of the
+// picks left the ladder and the second launch alone took 0.38 ms.
+// Control flow is uniform across the wavefront but for the layer and step
+// loops, where lanes of other models or step counts drop out; finished groups
+// go on evaluating until all are done.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 
 #include "masw.h"
@@ -53,9 +73,13 @@
 namespace masw {
 namespace {
 
-constexpr int kClassifyWaves = 4;           // wavefronts (wavelengths) per workgroup
+constexpr int kClassifyWaves = 4;           // wavefronts per workgroup
+constexpr int kGroup = 8;                   // lanes per wavelength
+constexpr int kGroups = 64 / kGroup;        // wavelengths per wavefront
 constexpr int kMaxStepsPerLayer = 1 << 16;  // beyond this a layer is not crossed
-constexpr int kMaxRounds = 8;               // 63^8 > 2e14
+constexpr int kMaxRounds = 4;               // of a pick's eight lanes, before it is deferred
+constexpr int kMaxWideRounds = 8;           // of a deferred pick's 64 lanes: 63^8 > 2e14
+constexpr int kDeferred = -2;               // a deferred pick's class between the two launches
 constexpr int kTerms = 12;                  // series terms, |U|, |W| <= 1
 constexpr double kRootTol = 1e-12;
 
@@ -164,30 +188,54 @@ __device__ __forceinline__ void step_propagator(const SysMat& m, double u, doubl
   P[2 * 4 + 3] = -__builtin_fma(b1, yxy11, b0 * m.a23);
 }
 
-// Replace the columns (x, y) by a nearly orthonormal basis of their span
-// with the same orientation: x divided by about its norm, then y less its
-// component along x and divided by about its norm.  Only the span, the
-// orientation (both divisors positive) and a well-conditioned basis matter to
-// the sign and the zeros of F, so the hardware reciprocal square root
-// (relative error below 2^-21) serves as the divisor without refinement.
-__device__ __forceinline__ void orthonormalize(double x[4], double y[4]) {
-  const double ix = __builtin_amdgcn_rsq(x[0] * x[0] + x[1] * x[1] + x[2] * x[2] + x[3] * x[3]);
+// 1/x: the hardware estimate (within 2^-21 relative) and one third-order step,
+// r (1 + e + e^2) with e = 1 - x r.
+__device__ __forceinline__ double inv(double x) {
+  const double r = __builtin_amdgcn_rcp(x);
+  const double e = __builtin_fma(-x, r, 1.0);
+  return __builtin_fma(r, __builtin_fma(e, e, e), r);
+}
+
+// 1/sqrt(x): the hardware estimate (within 2^-21 relative) and one Newton step.
+__device__ __forceinline__ double inv_sqrt(double x) {
+  const double y = __builtin_amdgcn_rsq(x);
+  return __builtin_fma(0.5 * y, __builtin_fma(-(x * y), y, 1.0), y);
+}
+
+// Replace the columns (x, y) by an orthonormal basis of their span with the
+// same orientation: x divided by its norm, then y less its component along x
+// and divided by its norm.  Returns the product of the two reciprocal norms
+// (positive), by which every 2x2 minor of (x, y) is multiplied.
+__device__ __forceinline__ double orthonormalize(double x[4], double y[4]) {
+  const double ix = inv_sqrt(x[0] * x[0] + x[1] * x[1] + x[2] * x[2] + x[3] * x[3]);
 #pragma unroll
   for (int i = 0; i < 4; ++i) x[i] *= ix;
   const double d = x[0] * y[0] + x[1] * y[1] + x[2] * y[2] + x[3] * y[3];
 #pragma unroll
   for (int i = 0; i < 4; ++i) y[i] = __builtin_fma(-d, x[i], y[i]);
-  const double iy = __builtin_amdgcn_rsq(y[0] * y[0] + y[1] * y[1] + y[2] * y[2] + y[3] * y[3]);
+  const double iy = inv_sqrt(y[0] * y[0] + y[1] * y[1] + y[2] * y[2] + y[3] * y[3]);
 #pragma unroll
   for (int i = 0; i < 4; ++i) y[i] *= iy;
+  return ix * iy;
 }
 
 // F(c) for wavenumber k and a model of N layers over a half-space (values at
-// index N); c below the half-space's beta.  NaN if a layer needs more than
-// kMaxStepsPerLayer steps.
-__device__ double secular(double c, double k, const double* __restrict__ h, const double* __restrict__ al,
-                          const double* __restrict__ be, const double* __restrict__ rh, int N,
-                          unsigned* steps_taken) {
+// index N); c in the bracket [sqrt(c2_lo), sqrt(c2_hi)] below the
+// half-space's beta.  Each layer's step count is the larger of the two ends'
+// (max(|u|, |w|) is largest at an end: both are linear in c^2).  NaN if a
+// layer needs more than kMaxStepsPerLayer steps.
+// The value is *mant 2^*expo: the orthonormalisations' divisors are multiplied
+// back in (their exponents apart, so nothing overflows), which makes it the
+// analytic dispersion function.  Without them F is +-sin of an angle between
+// planes, which near a mode of a slow layer turns over within a tiny part of
+// a grid step, where interpolation says nothing.
+struct Secular {
+  double mant;
+  int expo;
+};
+__device__ Secular secular(double c, double c2_lo, double c2_hi, double k, const double* __restrict__ h,
+                           const double* __restrict__ al, const double* __restrict__ be,
+                           const double* __restrict__ rh, int N, unsigned* steps_taken) {
   const double c2 = c * c;
   const double mu_ref = rh[N] * be[N] * be[N];
   const double i_ref = 1.0 / mu_ref;
@@ -196,22 +244,26 @@ __device__ double secular(double c, double k, const double* __restrict__ h, cons
   const double s = __builtin_sqrt(1.0 - g);
   double x[4] = {1.0, r, -2.0 * r, g - 2.0};
   double y[4] = {s, 1.0, g - 2.0, -2.0 * s};
-  orthonormalize(x, y);
+  int expo = 0;
+  double scale = __builtin_frexp(orthonormalize(x, y), &expo);  // product of reciprocal norms: scale 2^expo
   for (int j = N - 1; j >= 0; --j) {
     const double a = al[j], b = be[j], rho = rh[j];
     const double M = rho * a * a, mu = rho * b * b;
-    const double iM = 1.0 / M, imu = 1.0 / mu;
+    const double iM = inv(M), imu = inv(mu);
     const double rc2 = rho * c2;
     const double u = 1.0 - rc2 * iM;   // 1 - c^2/alpha^2
     const double w = 1.0 - rc2 * imu;  // 1 - c^2/beta^2
-    const double q = __builtin_sqrt(__builtin_fmax(__builtin_fabs(u), __builtin_fabs(w)));
+    const double pa = rho * iM, pb = rho * imu;  // 1/alpha^2, 1/beta^2
+    const double e_lo = __builtin_fmax(__builtin_fabs(1.0 - c2_lo * pa), __builtin_fabs(1.0 - c2_lo * pb));
+    const double e_hi = __builtin_fmax(__builtin_fabs(1.0 - c2_hi * pa), __builtin_fabs(1.0 - c2_hi * pb));
+    const double q = __builtin_sqrt(__builtin_fmax(e_lo, e_hi));
     const double kh = k * h[j];
     const double need = __builtin_ceil(kh * q);
-    if (!(need <= double(kMaxStepsPerLayer))) return __builtin_nan("");
+    if (!(need <= double(kMaxStepsPerLayer))) return Secular{__builtin_nan(""), 0};
     const int steps = need < 1.0 ? 1 : int(need);
     *steps_taken += unsigned(steps);
     double P[16];
-    step_propagator(system_matrix(M, mu, iM, imu, rc2, mu_ref, i_ref), u, w, kh / double(steps), P);
+    step_propagator(system_matrix(M, mu, iM, imu, rc2, mu_ref, i_ref), u, w, kh * inv(double(steps)), P);
     for (int st = 0; st < steps; ++st) {
       double nx[4], ny[4];
 #pragma unroll
@@ -219,7 +271,9 @@ __device__ double secular(double c, double k, const double* __restrict__ h, cons
         nx[i] = P[i * 4 + 0] * x[0] + P[i * 4 + 1] * x[1] + P[i * 4 + 2] * x[2] + P[i * 4 + 3] * x[3];
         ny[i] = P[i * 4 + 0] * y[0] + P[i * 4 + 1] * y[1] + P[i * 4 + 2] * y[2] + P[i * 4 + 3] * y[3];
       }
-      orthonormalize(nx, ny);
+      int e;
+      scale = __builtin_frexp(scale * orthonormalize(nx, ny), &e);
+      expo += e;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         x[i] = nx[i];
@@ -227,7 +281,7 @@ __device__ double secular(double c, double k, const double* __restrict__ h, cons
       }
     }
   }
-  return x[2] * y[3] - y[2] * x[3];
+  return Secular{(x[2] * y[3] - y[2] * x[3]) / scale, -expo};
 }
 
 __device__ __forceinline__ int sgn(double v) { return int(v > 0.0) - int(v < 0.0); }
@@ -250,11 +304,16 @@ __device__ __forceinline__ unsigned xcd_block(unsigned b, unsigned nb) {
   return base + (w % kXcds) * kXcdRun + w / kXcds;
 }
 
-// Class and root of wavelength wl, by one whole wavefront.  Returns the
-// multisection rounds run (uniform across the wavefront); *steps gets this
-// lane's propagator steps and *n_layers the model's layer count.
-__device__ int classify_one(const ClassifyArgsDev& a, int64_t wl, int lane, int* cls_out, double* root_out,
-                            unsigned* steps_out, int* n_layers) {
+// The model and bracket that a lane evaluates.
+struct LaneWork {
+  const double *h, *al, *be, *rh;
+  double k, c_lo, c_hi;
+  int N;
+};
+
+// Wavelength wl as eight lanes (`sub` the lane among them) see it: its model,
+// k and bracket, and its class where no evaluation is needed, else -1.
+__device__ int lane_work(const ClassifyArgsDev& a, int64_t wl, int sub, unsigned long long group, LaneWork* o) {
   // model of wavelength wl: lambda_off[m] <= wl < lambda_off[m + 1]
   int m_lo = 0, m_hi = a.n_models;
   while (m_hi - m_lo > 1) {
@@ -263,100 +322,83 @@ __device__ int classify_one(const ClassifyArgsDev& a, int64_t wl, int lane, int*
   }
   const int m = m_lo;
   const int N = a.layer_off[m + 1] - a.layer_off[m];
-  const double* h = a.h + a.layer_off[m];
   const int64_t r0 = int64_t(a.layer_off[m]) + m;
-  const double* al = a.alpha + r0;
-  const double* be = a.beta + r0;
-  const double* rh = a.rho + r0;
+  o->h = a.h + a.layer_off[m];
+  o->al = a.alpha + r0;
+  o->be = a.beta + r0;
+  o->rh = a.rho + r0;
+  o->N = N;
   const int i = a.idx[wl];
-
-  int cls;
-  double root = __builtin_nan("");
-  unsigned steps = 0;  // propagator steps of this lane
-  int rounds = 0;
-  if (i < 1 || i >= a.n_c) {
-    cls = MASW_PICK_NONE;
-  } else {
-    // device validation of the model, the wavelength and the bracket
-    bool bad = (N < 0 || N > MASW_MAX_LAYERS);
-    for (int j = lane; !bad && j <= N; j += 64) {
-      const double aj = al[j], bj = be[j], rj = rh[j];
-      bool ok = finite_pos(aj) && finite_pos(bj) && finite_pos(rj) && aj > bj;
-      if (j < N) ok = ok && finite_pos(h[j]);
-      bad = !ok;
-    }
-    const double lam = a.lambda[wl];
-    const double c_lo0 = a.c[i - 1], c_hi0 = a.c[i];
-    bad = bad || !finite_pos(lam) || !finite_pos(c_lo0) || !finite_pos(c_hi0) || !(c_hi0 > c_lo0);
-    if (__ballot(bad) != 0ull) {
-      cls = MASW_PICK_INVALID;
-    } else if (c_hi0 >= be[N]) {
-      cls = MASW_PICK_LEAKY;
-    } else {
-      const double k = 2.0 * 3.14159265358979323846 / lam;
-      const double tol = kRootTol * c_hi0;
-      double lo = c_lo0, hi = c_hi0;
-      int s_lo = 0;
-      cls = MASW_PICK_MODE;
-      for (int round = 0; round < kMaxRounds; ++round) {
-        const double cl = lane == 63 ? hi : __builtin_fma(hi - lo, double(lane) * (1.0 / 63.0), lo);
-        const double F = secular(cl, k, h, al, be, rh, N, &steps);
-        ++rounds;
-        const bool nan = !(F == F) || !(__builtin_fabs(F) < __builtin_inf());
-        if (__ballot(nan) != 0ull) {
-          cls = MASW_PICK_UNRESOLVED;
-          break;
-        }
-        const int sg = sgn(F);
-        if (round == 0) {
-          s_lo = __shfl(sg, 0, 64);
-          if (__shfl(sg, 63, 64) == s_lo) {
-            cls = MASW_PICK_POLE;
-            break;
-          }
-        }
-        // first point whose sign differs from the lower end's (lane 63 does)
-        const uint64_t diff = __ballot(lane >= 1 && sg != s_lo);
-        const int l = __builtin_ctzll(diff);
-        lo = __shfl(cl, l - 1, 64);
-        hi = __shfl(cl, l, 64);
-        if (hi - lo <= tol) break;
-      }
-      if (cls == MASW_PICK_MODE) root = 0.5 * (lo + hi);
-    }
+  if (i < 1 || i >= a.n_c) return MASW_PICK_NONE;
+  // device validation of the model, the wavelength and the bracket
+  bool bad = (N < 0 || N > MASW_MAX_LAYERS);
+  for (int j = sub; !bad && j <= N; j += kGroup) {
+    const double aj = o->al[j], bj = o->be[j], rj = o->rh[j];
+    bool ok = finite_pos(aj) && finite_pos(bj) && finite_pos(rj) && aj > bj;
+    if (j < N) ok = ok && finite_pos(o->h[j]);
+    bad = !ok;
   }
-  *cls_out = cls;
-  *root_out = root;
-  *steps_out = steps;
-  *n_layers = N;
-  return rounds;
+  const double lam = a.lambda[wl];
+  o->c_lo = a.c[i - 1];
+  o->c_hi = a.c[i];
+  bad = bad || !finite_pos(lam) || !finite_pos(o->c_lo) || !finite_pos(o->c_hi) || !(o->c_hi > o->c_lo);
+  o->k = 2.0 * 3.14159265358979323846 / lam;
+  // (the eight lanes are converged here: they share wl)
+  if ((__ballot(bad) & group) != 0ull) return MASW_PICK_INVALID;
+  return o->c_hi >= o->be[N] ? MASW_PICK_LEAKY : -1;
 }
 
-__global__ __launch_bounds__(64 * kClassifyWaves) void classify_kernel(ClassifyArgsDev a) {
-  __shared__ unsigned long long s_cnt[kClassifyWaves][3];
-  const int lane = int(threadIdx.x) & 63;
-  const int wave = int(threadIdx.x) >> 6;
-  const unsigned vb = xcd_block(blockIdx.x, gridDim.x);
-  const int64_t wl = int64_t(vb) * kClassifyWaves + wave;
-  unsigned long long n_eval = 0, n_layer = 0, n_step = 0;
-  if (wl < a.n_lam) {  // uniform across the wavefront
-    int cls, N;
-    double root;
-    unsigned steps;
-    const int rounds = classify_one(a, wl, lane, &cls, &root, &steps, &N);
-    n_step = steps;
+// Root, in units of the spacing from the first point, of the polynomial
+// through the group's eight values at equally spaced points, between points
+// l - 1 and l where the sign changes: forward differences and secant steps
+// on Newton's form.
+__device__ double poly_root(const Secular& v, int l) {
+  int top = v.expo;  // the values at one common exponent, the largest
 #pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) n_step += __shfl_xor(n_step, off, 64);
-    n_eval = 64ull * unsigned(rounds);
-    n_layer = n_eval * unsigned(N);
-    if (lane == 0) {
-      a.cls[wl] = cls;
-      if (a.c_sec) a.c_sec[wl] = root;
+  for (int off = kGroup / 2; off >= 1; off >>= 1) top = max(top, __shfl_xor(top, off, kGroup));
+  const double F = __builtin_ldexp(v.mant, max(-2000, v.expo - top));
+  double d[kGroup];
+#pragma unroll
+  for (int i = 0; i < kGroup; ++i) d[i] = __shfl(F, i, kGroup);
+  double t0 = double(l - 1), t1 = double(l);
+  double f0 = __shfl(F, l - 1, kGroup), f1 = __shfl(F, l, kGroup);
+#pragma unroll
+  for (int n = 1; n < kGroup; ++n)
+#pragma unroll
+    for (int i = kGroup - 1; i >= n; --i) d[i] -= d[i - 1];
+  const double a = t0, b = t1;
+  double t = t0 - f0 * (t1 - t0) / (f1 - f0);
+  for (int it = 0; it < 4; ++it) {
+    double p = d[kGroup - 1];
+#pragma unroll
+    for (int n = kGroup - 2; n >= 0; --n) p = __builtin_fma(p * (t - double(n)), 1.0 / double(n + 1), d[n]);
+    // secant step from the end of the pair that is nearer in value
+    if (__builtin_fabs(f1) < __builtin_fabs(f0)) {
+      t0 = t1;
+      f0 = f1;
     }
+    t1 = t;
+    f1 = p;
+    const double s = f1 - f0;
+    if (!(s != 0.0)) break;
+    t = t1 - f1 * (t1 - t0) / s;
+    t = __builtin_fmin(__builtin_fmax(t, a), b);
   }
-  // work counters: summed over the workgroup in LDS, one atomic per counter
-  // and workgroup (device-scope atomics bypass the L2, so each costs a
-  // memory write)
+  return t == t ? t : 0.5 * (a + b);
+}
+
+// Adds a wavefront's evaluations and this lane's layers and steps to the
+// call's counters: summed over the workgroup in LDS, one atomic per counter
+// and workgroup (device-scope atomics bypass the L2, so each costs a memory
+// write).  Called by every wavefront of the workgroup.
+__device__ void add_counts(const ClassifyArgsDev& a, unsigned long long (*s_cnt)[3], unsigned long long n_eval,
+                           unsigned long long n_layer, unsigned long long n_step) {
+  const int lane = int(threadIdx.x) & 63, wave = int(threadIdx.x) >> 6;
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) {
+    n_step += __shfl_xor(n_step, off, 64);
+    n_layer += __shfl_xor(n_layer, off, 64);
+  }
   if (lane == 0) {
     s_cnt[wave][0] = n_eval;
     s_cnt[wave][1] = n_layer;
@@ -369,6 +411,152 @@ __global__ __launch_bounds__(64 * kClassifyWaves) void classify_kernel(ClassifyA
     for (int w = 0; w < kClassifyWaves; ++w) sum += s_cnt[w][threadIdx.x];
     if (sum) atomicAdd(&a.counters[threadIdx.x], sum);
   }
+}
+
+__global__ __launch_bounds__(64 * kClassifyWaves) void classify_kernel(ClassifyArgsDev a) {
+  __shared__ unsigned long long s_cnt[kClassifyWaves][3];
+  const int lane = int(threadIdx.x) & 63;
+  const int wave = int(threadIdx.x) >> 6;
+  const int sub = lane & (kGroup - 1);
+  const unsigned long long group = 0xffull << (lane & ~(kGroup - 1));
+  const unsigned vb = xcd_block(blockIdx.x, gridDim.x);
+  const int64_t wl = (int64_t(vb) * kClassifyWaves + wave) * kGroups + (lane / kGroup);
+  unsigned rounds = 0, steps = 0;
+  LaneWork w{};
+  int cls = MASW_PICK_NONE;
+  if (wl < a.n_lam) cls = lane_work(a, wl, sub, group, &w);
+  double root = __builtin_nan("");
+  const unsigned long long todo = __ballot(cls < 0);
+  if (todo != 0ull) {
+    // lanes without an evaluation of their own mirror the first that has one
+    const int src = __ffsll((long long)todo) - 1;
+    const int64_t wl_src = __shfl(wl, src, 64);
+    bool done = cls >= 0;
+    if (done) {
+      LaneWork o{};
+      (void)lane_work(a, wl_src, sub, group, &o);
+      w = o;
+    }
+    const double tol = kRootTol * w.c_hi;
+    const double c2_lo = w.c_lo * w.c_lo, c2_hi = w.c_hi * w.c_hi;
+    // the ladder, in units of tol: this lane's offset from the root estimate
+    const double rung = (sub & 4) ? 1.0 : -1.0;
+    const int step = (sub & 4) ? (sub & 3) : 3 - (sub & 3);
+    const double offset = rung * tol * (step == 0 ? 0.45 : step == 1 ? 16.0 : step == 2 ? 2048.0 : 524288.0);
+    double lo = w.c_lo, hi = w.c_hi, est = 0.0;
+    Secular F_lo{0.0, 0}, F_hi{0.0, 0};
+    int s_lo = 0;
+    for (int round = 0; round < kMaxRounds; ++round) {
+      const double span = hi - lo;
+      double cl;
+      if (round == 0)
+        cl = sub == kGroup - 1 ? hi : __builtin_fma(span, double(sub) * (1.0 / 7.0), lo);
+      else
+        cl = __builtin_fmin(__builtin_fmax(est + offset, lo), hi);
+      const Secular F = secular(cl, c2_lo, c2_hi, w.k, w.h, w.al, w.be, w.rh, w.N, &steps);
+      ++rounds;
+      const bool nan = !(__builtin_fabs(F.mant) < __builtin_inf());
+      const int sg = sgn(F.mant);
+      const int s_first = __shfl(sg, 0, kGroup), s_last = __shfl(sg, kGroup - 1, kGroup);
+      if (round == 0) s_lo = s_first;
+      const unsigned long long nans = __ballot(nan) & group;
+      // first point whose sign differs from the lower end's (kGroup: none)
+      const unsigned diff = unsigned((__ballot(sg != s_lo) & group) >> (lane & ~(kGroup - 1)));
+      const int l = diff ? __ffs(int(diff)) - 1 : kGroup;
+      const double c_l = __shfl(cl, l & 7, kGroup), c_b = __shfl(cl, (l - 1) & 7, kGroup);
+      const Secular F_l{__shfl(F.mant, l & 7, kGroup), __shfl(F.expo, l & 7, kGroup)};
+      const Secular F_b{__shfl(F.mant, (l - 1) & 7, kGroup), __shfl(F.expo, (l - 1) & 7, kGroup)};
+      const double t = round == 0 ? poly_root(F, l < 1 || l > 7 ? 1 : l) : 0.0;
+      if (!done) {
+        if (nans) {
+          cls = MASW_PICK_UNRESOLVED;
+          done = true;
+        } else if (round == 0 && s_last == s_lo) {
+          cls = MASW_PICK_POLE;
+          done = true;
+        } else {
+          if (l > 0) {
+            lo = c_b;
+            F_lo = F_b;
+          }
+          if (l < kGroup) {
+            hi = c_l;
+            F_hi = F_l;
+          }
+          if (hi - lo <= tol) {
+            cls = MASW_PICK_MODE;
+            root = 0.5 * (lo + hi);
+            done = true;
+          } else if (round == 0) {
+            est = __builtin_fma(span, t * (1.0 / 7.0), w.c_lo);
+          } else if (l == 0 || l == kGroup || round == kMaxRounds - 1) {
+            cls = kDeferred;
+            done = true;
+          } else {
+            const double q = __builtin_ldexp(F_hi.mant / F_lo.mant, max(-1000, min(1000, F_hi.expo - F_lo.expo)));
+            est = lo + (hi - lo) / (1.0 - q);
+            if (!(est >= lo && est <= hi)) est = 0.5 * (lo + hi);
+          }
+        }
+      }
+      if (__ballot(!done) == 0ull) break;
+    }
+  }
+  if (wl < a.n_lam && sub == 0) {
+    a.cls[wl] = cls;
+    if (a.c_sec) a.c_sec[wl] = root;
+  }
+  add_counts(a, s_cnt, 64ull * rounds, rounds * (unsigned long long)unsigned(max(w.N, 0)), steps);
+}
+
+// The deferred picks, one whole wavefront each: multisection with 64 equally
+// spaced points a round, the first whose sign differs from the lower end's
+// giving the next bracket, 63 times narrower.  A wavefront looks through
+// every gridDim-th pick, so that neighbouring picks, which are often deferred
+// together, go to different ones.
+__global__ __launch_bounds__(64 * kClassifyWaves) void classify_deferred_kernel(ClassifyArgsDev a) {
+  __shared__ unsigned long long s_cnt[kClassifyWaves][3];
+  const int lane = int(threadIdx.x) & 63;
+  const int64_t n_waves = int64_t(gridDim.x) * kClassifyWaves;
+  const int64_t first = int64_t(blockIdx.x) * kClassifyWaves + (threadIdx.x >> 6);
+  unsigned long long n_eval = 0, n_layer = 0;
+  unsigned steps = 0;
+  for (int64_t base = first; base < a.n_lam; base += 64 * n_waves) {
+    const int64_t mine = base + lane * n_waves;
+    unsigned long long todo = __ballot(mine < a.n_lam && a.cls[mine < a.n_lam ? mine : 0] == kDeferred);
+    for (; todo != 0ull; todo &= todo - 1) {
+      const int64_t wl = base + (__ffsll((long long)todo) - 1) * n_waves;
+      LaneWork w{};
+      (void)lane_work(a, wl, lane & (kGroup - 1), ~0ull, &w);
+      const double tol = kRootTol * w.c_hi;
+      const double c2_lo = w.c_lo * w.c_lo, c2_hi = w.c_hi * w.c_hi;
+      double lo = w.c_lo, hi = w.c_hi;
+      int s_lo = 0, cls = MASW_PICK_MODE;
+      for (int round = 0; round < kMaxWideRounds; ++round) {
+        const double cl = lane == 63 ? hi : __builtin_fma(hi - lo, double(lane) * (1.0 / 63.0), lo);
+        const double F = secular(cl, c2_lo, c2_hi, w.k, w.h, w.al, w.be, w.rh, w.N, &steps).mant;
+        n_eval += 64;
+        n_layer += unsigned(w.N);
+        if (__ballot(!(__builtin_fabs(F) < __builtin_inf())) != 0ull) {
+          cls = MASW_PICK_UNRESOLVED;
+          break;
+        }
+        const int sg = sgn(F);
+        if (round == 0) s_lo = __shfl(sg, 0, 64);
+        // (lane 63's sign differs: it did in the first launch)
+        const unsigned long long diff = __ballot(lane >= 1 && sg != s_lo);
+        const int l = diff ? __ffsll((long long)diff) - 1 : 63;
+        lo = __shfl(cl, l - 1, 64);
+        hi = __shfl(cl, l, 64);
+        if (hi - lo <= tol) break;
+      }
+      if (lane == 0) {
+        a.cls[wl] = cls;
+        if (a.c_sec) a.c_sec[wl] = cls == MASW_PICK_MODE ? 0.5 * (lo + hi) : __builtin_nan("");
+      }
+    }
+  }
+  add_counts(a, s_cnt, n_eval, n_layer, steps);
 }
 
 __global__ void clear_counters_kernel(unsigned long long* c) {
@@ -398,8 +586,12 @@ hipError_t launch_classify(const ClassifyArgs& in, hipStream_t s) {
   a.counters = reinterpret_cast<unsigned long long*>(in.counters);
   // a kernel, not a memset, clears the counters, so a caller may capture the call
   hipLaunchKernelGGL(clear_counters_kernel, dim3(1), dim3(64), 0, s, a.counters);
-  const int64_t blocks = (in.n_lam + kClassifyWaves - 1) / kClassifyWaves;
+  constexpr int kPerBlock = kClassifyWaves * kGroups;  // wavelengths per workgroup
+  const int64_t blocks = (in.n_lam + kPerBlock - 1) / kPerBlock;
   hipLaunchKernelGGL(classify_kernel, dim3(unsigned(blocks)), dim3(64 * kClassifyWaves), 0, s, a);
+  // few picks are deferred: a fixed number of wavefronts looks for them
+  const int64_t wide = std::min<int64_t>(512, (in.n_lam + kClassifyWaves - 1) / kClassifyWaves);
+  hipLaunchKernelGGL(classify_deferred_kernel, dim3(unsigned(wide)), dim3(64 * kClassifyWaves), 0, s, a);
   return hipGetLastError();
 }
 

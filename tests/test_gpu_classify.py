@@ -195,3 +195,39 @@ def test_device_pointers_match_host_and_validate_on_device(ctx):
     assert np.all(cls_b[lo:hi][has_bracket] == M.MASW_PICK_INVALID)
     assert np.all(cls_b[lo:hi][~has_bracket] == M.MASW_PICK_NONE)
     assert np.array_equal(cls_b[:lo], cls_h[:lo]) and np.array_equal(cls_b[hi:], cls_h[hi:])
+
+
+# Eight wavelengths share a wavefront, 32 a workgroup: counts around both, on
+# models that change inside a wavefront, give what each pick gives alone.
+@pytest.mark.parametrize("n", [1, 7, 8, 9, 31, 33, 65])
+def test_groups_of_a_wavefront_are_independent(ctx, n):
+    wl = WL.batch_case(n_models=3, seed=21)
+    models = [WL.two_layer_model()] + wl.models[:2]
+    cut = sorted({0, n // 3, n // 2, n})
+    lams = [WL.log_spaced(1.0, 30.0, max(b - a, 0)) for a, b in zip(cut[:-1], cut[1:])]
+    models = models[:len(lams)]
+    c = WL.uniform_grid(50.0, 0.1, 9501)
+    _, idx, _, _ = ctx.batch(c, models, lams, prec=M.MASW_PREC_FP64)
+    idx[n // 4] = 0                                   # one without a bracket among them
+    cls, sec = ctx.classify(c, models, lams, idx)
+    for w, (m, lam) in enumerate(_expand(models, lams)):
+        one_cls, one_sec = ctx.classify(c, [m], [np.array([lam])], idx[w:w + 1])
+        assert cls[w] == one_cls[0]
+        assert sec[w] == one_sec[0] or (np.isnan(sec[w]) and np.isnan(one_sec[0]))
+
+
+# A bracket 122 m/s wide, where no polynomial through eight values of F gives
+# the root to the ladder's 5e-7: the picks are deferred to the second launch.
+# Both sides end on a bracket of 1e-12 c around the one root, so they differ by
+# 1e-12 and F's rounding there; ten times that is allowed.
+def test_deferred_picks_match_the_oracle(ctx):
+    m = WL.two_layer_model()
+    lam = WL.log_spaced(4.0, 10.9, 8)
+    c = np.array([100.0, 222.0, 300.0])
+    idx = np.ones(8, np.int32)
+    cls, sec = ctx.classify(c, [m], [lam], idx)
+    assert ctx.stats()["classify_evals"] > 4 * 64     # more than the first launch can make
+    for w in range(8):
+        want_cls, want_sec = PR.classify(float(lam[w]), c, 1, m)
+        assert cls[w] == want_cls == PR.PICK_MODE
+        assert abs(sec[w] - want_sec) <= 1e-11 * want_sec
