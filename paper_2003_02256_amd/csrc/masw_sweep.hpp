@@ -35,44 +35,76 @@ namespace masw {
 // ------------------------------------------------------------ utilities --
 __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
+// v of the previous lane (of lane l - 1, in lane l); lane 0 keeps its own.
+__device__ __forceinline__ int previous_lane(int v) {
+  constexpr int kWaveShr1 = 0x138;  // DPP: a shift by one lane across the wavefront
+  return __builtin_amdgcn_update_dpp(v, v, kWaveShr1, 0xf, 0xf, false);
+}
+
+// What one wavefront has to say about its 64 positions of a round, in one
+// LDS word pair: the sign codes at its first and last positions, the first
+// change inside it plus one (0: none), and the codes at and before that.
+struct WaveSum {
+  int32_t ends;   // first | last << 8 | (change + 1) << 16
+  int32_t pair;   // at | before << 8
+};
+
 // First sign change in one round of G*64 consecutive positions, one per
 // thread (position = round base + threadIdx.x).  `prev0` is the sign of the
 // position before the round (kNoSign if none).  A position whose predecessor
 // has no sign never counts as a change.  Returns the uniform offset in the
 // round of the first change, or -1; *carry receives the last thread's sign.
 // *sig_at / *prev_at receive the signs at the change (for NaN reporting).
+// One barrier: each wavefront publishes its WaveSum in sum[] and then
+// resolves all G of them, one per lane, by itself.  The caller alternates
+// between two buffers from round to round, or has a barrier of its own
+// between rounds, so that no wavefront overwrites what another still reads.
+// The last signs, the first changes and the signs at the change, each
+// published behind a barrier of its own, took four barriers a round: 11.15 us
+// against 10.22 us for 30 wavelengths x 801 velocities of a two-layer model
+// (0.4 us of it from the fused launch's staging), 756 against 740 us for the
+// split sweep of 1000 x 115,001 over 20 layers.
 template <int G>
-__device__ __forceinline__ int round_first_change(int sg, int prev0, int* s_last, int* s_first,
-                                                  int* s_pair, int* carry, int* sig_at,
+__device__ __forceinline__ int round_first_change(int sg, int prev0, WaveSum* sum, int* carry, int* sig_at,
                                                   int* prev_at) {
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
-  const int up = __shfl_up(sg, 1, 64);
-  if (lane == 63) s_last[wave] = sg;
-  __syncthreads();
-  const int prev = (lane == 0) ? (wave == 0 ? prev0 : s_last[wave - 1]) : up;
-  const bool change = (sg != kNoSign) && (prev != kNoSign) && (sg != prev);
-  const unsigned long long mask = __ballot(change);
-  if (lane == 0) s_first[wave] = mask ? (__ffsll((long long)mask) - 1) : 64;
-  __syncthreads();
-  int first = -1;
-#pragma unroll
-  for (int w = 0; w < G; ++w) {
-    const int f = s_first[w];
-    if (first < 0 && f < 64) first = w * 64 + f;
+  const int up = previous_lane(sg);
+  if constexpr (G == 1) {
+    const int prev = lane == 0 ? prev0 : up;
+    const unsigned long long hit = __ballot(sg != kNoSign && prev != kNoSign && sg != prev);
+    *carry = __builtin_amdgcn_readlane(sg, 63);
+    if (hit == 0ull) return -1;
+    const int f = __ffsll((long long)hit) - 1;
+    *sig_at = __builtin_amdgcn_readlane(sg, f);
+    *prev_at = __builtin_amdgcn_readlane(prev, f);
+    return f;
   }
-  if (first >= 0 && (int)threadIdx.x == first) {
-    s_pair[0] = sg;
-    s_pair[1] = prev;
-  }
-  *carry = s_last[G - 1];
+  const unsigned long long mask = __ballot(lane > 0 && sg != kNoSign && up != kNoSign && sg != up);
+  const int f = mask ? __ffsll((long long)mask) - 1 : 0;  // (lane 0 is never in the mask)
+  int first = __builtin_amdgcn_readfirstlane(sg), last = __builtin_amdgcn_readlane(sg, 63);
+  int at = __builtin_amdgcn_readlane(sg, f), before = __builtin_amdgcn_readlane(up, f);
+  int change = mask ? f + 1 : 0;
+  if (lane == 0)
+    sum[wave] = WaveSum{(first & 0xff) | (last & 0xff) << 8 | change << 16, (at & 0xff) | (before & 0xff) << 8};
   __syncthreads();
-  if (first >= 0) {
-    *sig_at = s_pair[0];
-    *prev_at = s_pair[1];
-  }
-  __syncthreads();
-  return first;
+  const WaveSum ws = sum[lane < G ? lane : 0];
+  first = int8_t(ws.ends);
+  last = int8_t(ws.ends >> 8);
+  change = ws.ends >> 16;
+  at = int8_t(ws.pair);
+  before = int8_t(ws.pair >> 8);
+  // lane w < G: wavefront w, whose predecessor is the last sign of w - 1
+  const int last_up = previous_lane(last);
+  const int prev = lane == 0 ? prev0 : last_up;
+  const bool edge = first != kNoSign && prev != kNoSign && first != prev;
+  const unsigned long long hit = __ballot(lane < G && (edge || change > 0));
+  *carry = __builtin_amdgcn_readlane(last, G - 1);
+  if (hit == 0ull) return -1;
+  const int w = __ffsll((long long)hit) - 1;
+  *sig_at = __builtin_amdgcn_readlane(edge ? first : at, w);
+  *prev_at = __builtin_amdgcn_readlane(edge ? prev : before, w);
+  return w * 64 + __builtin_amdgcn_readlane(edge ? 0 : change - 1, w);
 }
 
 // Sweep code of a grid point in the FP32 sweep: the determinant's sign code,
@@ -96,10 +128,9 @@ enum { kModeFP64 = 0, kModeSplit = 1 };
 template <int G>
 struct SweepShared {
   int item;
-  int last[G];
   int first[G];
-  int pair[2];
   int check[8];
+  WaveSum sum[2][G];
   int coop[6];
 };
 
@@ -191,7 +222,8 @@ constexpr CoopRef kNoCoop{nullptr, nullptr, nullptr, 0};
 // Round rd of an item: positions rd*P .. rd*P+P-1, the first one with no
 // predecessor.  Returns the first change inside the round (uniform); *sl is
 // the sign at the last position (uniform), *sa/*pa the signs at the change
-// and before it, and thread 0's *s0 the sign at the first position.
+// and before it, and thread 0's *s0 the sign at the first position.  The
+// callers have barriers between rounds.
 template <typename T, int G>
 __device__ __forceinline__ int eval_round(const ItemRef& r, int rd, SweepShared<G>& sh, int* s0, int* sl,
                                           int* sa, int* pa) {
@@ -205,7 +237,7 @@ __device__ __forceinline__ int eval_round(const ItemRef& r, int rd, SweepShared<
       sg = sweep_code32(c32_at(r, i), float(r.k64), r.L32, r.N);
   }
   *s0 = sg;
-  return round_first_change<G>(sg, kNoSign, sh.last, sh.first, sh.pair, sl, sa, pa);
+  return round_first_change<G>(sg, kNoSign, sh.sum[0], sl, sa, pa);
 }
 
 // The owner's side of a shared sweep over the whole grid: the same first
@@ -404,7 +436,7 @@ __device__ bool run_item(const ItemRef& r, ItemState& st, int budget, SweepShare
           const int i = base + tid;
           const int sg = (i < n32) ? sweep_code32(c32_at(r, i), k32, r.L32, r.N) : kNoSign;
           int s_c, p_c;
-          const int f = round_first_change<G>(sg, carry, sh.last, sh.first, sh.pair, &carry, &s_c, &p_c);
+          const int f = round_first_change<G>(sg, carry, sh.sum[rounds & 1], &carry, &s_c, &p_c);
           wc.sweep += (unsigned long long)min(P, n32 - base);
           if (f >= 0) {
             cand = base + f;
@@ -530,7 +562,7 @@ __device__ bool run_item(const ItemRef& r, ItemState& st, int budget, SweepShare
       ++rounds;
       const int i = base + tid;
       const int sg = (i < n_c) ? det_sign<double, false>(r.c64[i], r.k64, r.L64, r.N, nullptr) : kNoSign;
-      const int f = round_first_change<G>(sg, carry, sh.last, sh.first, sh.pair, &carry, &sig_f, &prev_f);
+      const int f = round_first_change<G>(sg, carry, sh.sum[rounds & 1], &carry, &sig_f, &prev_f);
       wc.sweep += (unsigned long long)min(P, n_c - base);
       if (f >= 0) {
         found = base + f;
@@ -802,7 +834,9 @@ __global__ __launch_bounds__(64 * kFusedG) void fused_sweep_kernel(SweepArgs a) 
   LayerRec64* L64 = reinterpret_cast<LayerRec64*>(fused_lds);
   LayerRec32* L32 = reinterpret_cast<LayerRec32*>(fused_lds + sizeof(LayerRec64) * size_t(N + 1));
   stamp_start(a.tstamp, 0, 1);  // the job is this one launch
-  if (tid == 0) s_below = 0;
+  const int g = int(blockIdx.x);
+  const double lam = a.f_lambda[g];  // read here, so that its latency overlaps the checks
+  if (MODE == kModeSplit && tid == 0) s_below = 0;
   // the model: checks and records (build_model's)
   const double be_hs = a.f_beta[N];
   const double mu_ref = a.f_rho[N] * be_hs * be_hs;
@@ -848,12 +882,13 @@ __global__ __launch_bounds__(64 * kFusedG) void fused_sweep_kernel(SweepArgs a) 
     below += (c * c * ib2 < 1.0) ? 1 : 0;
   }
   const int bad = __syncthreads_or((lok && gok) ? 0 : 1);
-  for (int o = 32; o > 0; o >>= 1) below += __shfl_xor(below, o, 64);
-  if ((tid & 63) == 0 && below) atomicAdd(&s_below, below);
-  __syncthreads();
-  const int n_real = s_below;
-  const int g = int(blockIdx.x);
-  const double lam = a.f_lambda[g];
+  int n_real = 0;  // only the FP32 sweep asks for it
+  if constexpr (MODE == kModeSplit) {
+    for (int o = 32; o > 0; o >>= 1) below += __shfl_xor(below, o, 64);
+    if ((tid & 63) == 0 && below) atomicAdd(&s_below, below);
+    __syncthreads();
+    n_real = s_below;
+  }
   const bool ok = !bad && (lam > 0.0) && (lam < __builtin_inf());
   ItemRef r;
   r.N = bad ? 0 : N;
