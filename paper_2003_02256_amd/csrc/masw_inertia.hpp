@@ -14,10 +14,6 @@
 // E = J + P = s + 2P is non-decreasing, and s changes only where E does, so
 // the first change of sign(det K) along the grid is found by a search on E
 // instead of a walk (search() below):
-//   0. Prediction (when the picks of neighbouring wavelengths predict this
-//      one): counts at c_test[0], before a 62-point window around the
-//      prediction and in it; equal counts before the window prove no change
-//      there, and the window's first differing count is the change of E.
 //   1. Sampling: det K's sign at c_test[0] and 63 spread grid points; the
 //      first sampled sign that differs bounds the pick from above, so the
 //      counts stay at velocities near it (a layer needs more sublayers, see
@@ -54,7 +50,9 @@
 //
 // Each count costs one elimination of K plus, per layer above that bound,
 // one more element matrix and m - 1 pivots, against Algorithm 1's one
-// elimination per grid point up to the pick.  One wavefront per wavelength.
+// elimination per grid point up to the pick.  One wavefront per wavelength
+// here; masw_inertia_kernel.hpp has the search by fewer lanes for the usual
+// case E(c_test[0]) = 0, which leaves what it cannot settle to this one.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -234,7 +232,7 @@ constexpr int kResume = -3;  // a walk handed back to the caller (Tally::handoff
 // Algorithm 1's walk from grid index `start`, whose predecessor has sign
 // `carry`, one grid point per lane.  Returns the index of the first change
 // (-1 if none) and its signs, or kResume with t.handoff.
-__device__ inline int walk(const double* c64, int n_c, double k, const LayerRec64* L, int N, int start,
+__device__ __forceinline__ int walk(const double* c64, int n_c, double k, const LayerRec64* L, int N, int start,
                            int carry, int* sig_f, int* prev_f, Tally& t) {
   if (t.handoff) {
     t.resume = start;
@@ -305,27 +303,24 @@ struct Bracket {
 };
 constexpr int kLocated = -2;
 
-// Round B.  The first change of sign(det K) after a (sign sig0 on [0, a]) is
-// in (a, pf], pb the sampled point before pf.  Counts at a (lane 0; E_a if
-// `known`), at pb (lane 1) and at 62 points of (pb, pf].  Returns kLocated
-// with *br set, or the pick (-1: none) with its signs.
-__device__ inline int from_sampled_bound(const double* c64, int n_c, double k, const LayerRec64* L, int N, int a,
-                                         bool known, int E_a, int sig0, int pb, int pf, Bracket* br, int* sig_f,
-                                         int* prev_f, Tally& t) {
+// Round B.  The first change of sign(det K) (sig0 at c_test[0]) is in
+// (0, pf], pb the sampled point before pf.  Counts at c_test[0] (lane 0), at
+// pb (lane 1) and at 62 points of (pb, pf].  Returns kLocated with *br set,
+// or the pick (-1: none) with its signs.
+__device__ __forceinline__ int from_sampled_bound(const double* c64, int n_c, double k, const LayerRec64* L, int N, int sig0,
+                                         int pb, int pf, Bracket* br, int* sig_f, int* prev_f, Tally& t) {
   const int lane = threadIdx.x & 63;
   bool vb;
-  const int pbk = (lane == 0) ? a : (lane == 1 ? pb : spread(pb, pf, lane, 2, &vb));
+  const int pbk = (lane == 0) ? 0 : (lane == 1 ? pb : spread(pb, pf, lane, 2, &vb));
   if (lane < 2) vb = true;
-  const int E = (lane == 0 && known) ? E_a : (vb ? count_E(c64[pbk], k, L, N, t, lane != 1 || pb != a) : 0);
-  if (!known) {
-    E_a = __shfl(E, 0, 64);
-    if (E_a == kEvent) return walk(c64, n_c, k, L, N, a + 1, sig0, sig_f, prev_f, t);
-  }
+  const int E = vb ? count_E(c64[pbk], k, L, N, t, lane != 1 || pb != 0) : 0;
+  const int E_a = __shfl(E, 0, 64);
+  if (E_a == kEvent) return walk(c64, n_c, k, L, N, 1, sig0, sig_f, prev_f, t);
   const int E_b = __shfl(E, 1, 64);
   br->E_a = E_a;
   br->bound = pf;
   if (E_b != E_a) {
-    br->lo = a;  // a change of E before the sampled point before the bound
+    br->lo = 0;  // a change of E before the sampled point before the bound
     br->hi = pb;
     br->E_hi = E_b;
     return kLocated;
@@ -343,7 +338,7 @@ __device__ inline int from_sampled_bound(const double* c64, int n_c, double k, c
 // (the parity of E), and the search after a change of E that leaves the
 // sign unchanged (a mode and a pole, or two modes, in one step).  Returns the
 // pick (-1: none) with its signs.
-__device__ inline int finish(const double* c64, int n_c, double k, const LayerRec64* L, int N, int sig0, Bracket br,
+__device__ __forceinline__ int finish(const double* c64, int n_c, double k, const LayerRec64* L, int N, int sig0, Bracket br,
                              int* sig_f, int* prev_f, Tally& t) {
   const int n = n_c - 1;
   int lo = br.lo, hi = br.hi, E_a = br.E_a, E_hi = br.E_hi;
@@ -380,109 +375,49 @@ __device__ inline int finish(const double* c64, int n_c, double k, const LayerRe
 }
 
 // The pick of one wavelength (-1: none), with the determinant signs at it and
-// at its predecessor.  pred >= 1 predicts the pick (from the previous
-// wavelengths of the same model), or is -1.
-//   P. With a prediction: counts at c_test[0] (lane 0), at the grid point w0
-//      before a window of 62 consecutive grid points around the prediction
-//      (lane 1), and at the window's points.  E(w0) = E(c_test[0]) proves no
-//      change of E up to w0, and the first window point whose count differs
-//      is then the first change of E.  If E changes before w0 the counts
-//      narrow (0, w0]; if it changes in neither, the search goes on after
-//      the window (A, B).
-//   A. Determinant signs at the start point (lane 0) and 63 spread grid
-//      points after it.  A sampled sign that differs from the start's bounds
-//      the pick from above, so the counts that follow stay at velocities
-//      near it, where a layer needs few sublayers (their number grows with
-//      c).
-//   B. Counts at the start point, at the sampled point before that bound,
-//      and at 62 points between the two sampled points; then narrowing on E.
+// at its predecessor, by one whole wavefront.
+//   A. Determinant signs at c_test[0] (lane 0) and 63 spread grid points
+//      after it.  A sampled sign that differs from the first bounds the pick
+//      from above, so the counts that follow stay at velocities near it,
+//      where a layer needs few sublayers (their number grows with c).
+//   B. Counts at c_test[0], at the sampled point before that bound, and at
+//      62 points between the two sampled points; then narrowing on E.
 // With no sampled sign different (no change, or an even number of changes
-// between samples), the counts search the rest of the grid.
-__device__ inline int search(const double* c64, int n_c, double k, const LayerRec64* L, int N, int pred,
-                             int* sig_f, int* prev_f, Tally& t) {
+// between samples), the counts search the whole grid.
+__device__ __forceinline__ int search(const double* c64, int n_c, double k, const LayerRec64* L, int N, int* sig_f,
+                             int* prev_f, Tally& t) {
   const int lane = threadIdx.x & 63;
   const int n = n_c - 1;
-  int a = 0;         // no change of sign(det K) in [0, a]
-  int E_a = 0;       // E(a), once known
-  int sig0 = 0;      // sign(det K) on [0, a], once known
-  bool known = false;
-  bool located = false;  // (lo, hi] holds the first change of E after lo
-  int bound = n, lo = 0, hi = 0, E_hi = 0;
-  if (pred >= 1 && n >= 64) {
-    // P
-    const int w0 = max(0, min(pred - 32, n - 62));
-    const int p = (lane == 0) ? 0 : w0 + lane - 1;  // lanes 2..63: w0 + 1 .. w0 + 62 <= n
-    const int E = count_E(c64[p], k, L, N, t, lane != 1 || w0 > 0);
-    E_a = __shfl(E, 0, 64);
-    if (E_a == kEvent) {
-      sig0 = det_sign<double, false>(c64[0], k, L, N, nullptr);
-      ++t.check;
-      return walk(c64, n_c, k, L, N, 1, sig0, sig_f, prev_f, t);
-    }
-    sig0 = parity_sign(E_a);
-    known = true;
-    const int E_w = __shfl(E, 1, 64);
-    if (E_w != E_a) {  // a change of E in (0, w0]
-      hi = w0;
-      E_hi = E_w;
-      located = true;
-    } else {
-      const unsigned long long m = __ballot(lane >= 2 && E != E_a);
-      if (m) {
-        const int f = __ffsll((long long)m) - 1;
-        hi = __shfl(p, f, 64);
-        lo = __shfl(p, f - 1, 64);
-        E_hi = __shfl(E, f, 64);
-        located = true;
-      } else {
-        a = w0 + 62;  // no change up to the window's end
-      }
-    }
+  // A
+  bool va;
+  const int pa = (lane == 0) ? 0 : spread(0, n, lane, 1, &va);
+  if (lane == 0) va = true;
+  const int sa = va ? det_sign<double, false>(c64[pa], k, L, N, nullptr) : kNoSign;
+  t.check += (unsigned long long)(1 + min(63, n));
+  const int sig0 = __shfl(sa, 0, 64);
+  if (sig0 != 1 && sig0 != -1) return walk(c64, n_c, k, L, N, 1, sig0, sig_f, prev_f, t);
+  Bracket br;
+  const unsigned long long ma = __ballot(lane > 0 && va && sa != sig0);
+  if (ma) {
+    // B: the first change of sign(det K) is in (0, p_f]
+    const int f = __ffsll((long long)ma) - 1;
+    const int pf = __shfl(pa, f, 64), pb = __shfl(pa, f - 1, 64);
+    const int r = from_sampled_bound(c64, n_c, k, L, N, sig0, pb, pf, &br, sig_f, prev_f, t);
+    if (r != kLocated) return r;
+  } else {
+    // no sampled sign differs: counts at the sampled points
+    const int E0 = va ? count_E(c64[pa], k, L, N, t, true) : 0;
+    br.E_a = __shfl(E0, 0, 64);
+    br.bound = n;
+    if (br.E_a == kEvent) return walk(c64, n_c, k, L, N, 1, sig0, sig_f, prev_f, t);
+    const unsigned long long m0 = __ballot(lane > 0 && va && E0 != br.E_a);
+    if (!m0) return -1;  // no change of E: sign(det K) is constant
+    const int f = __ffsll((long long)m0) - 1;
+    br.hi = __shfl(pa, f, 64);
+    br.lo = __shfl(pa, f - 1, 64);
+    br.E_hi = __shfl(E0, f, 64);
   }
-  if (!located) {
-    // A
-    bool va;
-    const int pa = (lane == 0) ? a : spread(a, n, lane, 1, &va);
-    if (lane == 0) va = true;
-    const int sa =
-        (lane == 0 && known) ? sig0 : (va ? det_sign<double, false>(c64[pa], k, L, N, nullptr) : kNoSign);
-    t.check += (unsigned long long)((known ? 0 : 1) + min(63, n - a));
-    if (!known) {
-      sig0 = __shfl(sa, 0, 64);
-      if (sig0 != 1 && sig0 != -1) return walk(c64, n_c, k, L, N, 1, sig0, sig_f, prev_f, t);
-    }
-    const unsigned long long ma = __ballot(lane > 0 && va && sa != sig0);
-    if (ma) {
-      // B: the first change of sign(det K) after a is in (a, p_f]
-      const int f = __ffsll((long long)ma) - 1;
-      const int pf = __shfl(pa, f, 64), pb = __shfl(pa, f - 1, 64);
-      Bracket br;
-      const int r = from_sampled_bound(c64, n_c, k, L, N, a, known, E_a, sig0, pb, pf, &br, sig_f, prev_f, t);
-      if (r != kLocated) return r;
-      lo = br.lo;
-      hi = br.hi;
-      E_a = br.E_a;
-      E_hi = br.E_hi;
-      bound = br.bound;
-    } else {
-      // no sampled sign differs: counts over the rest of the grid
-      bool v0;
-      const int p0 = (lane == 0) ? a : spread(a, n, lane, 1, &v0);
-      if (lane == 0) v0 = true;
-      const int E0 = (lane == 0 && known) ? E_a : (v0 ? count_E(c64[p0], k, L, N, t, true) : 0);
-      if (!known) {
-        E_a = __shfl(E0, 0, 64);
-        if (E_a == kEvent) return walk(c64, n_c, k, L, N, a + 1, sig0, sig_f, prev_f, t);
-      }
-      const unsigned long long m0 = __ballot(lane > 0 && v0 && E0 != E_a);
-      if (!m0) return -1;  // no change of E after a: sign(det K) is constant
-      const int f = __ffsll((long long)m0) - 1;
-      hi = __shfl(p0, f, 64);
-      lo = __shfl(p0, f - 1, 64);
-      E_hi = __shfl(E0, f, 64);
-    }
-  }
-  return finish(c64, n_c, k, L, N, sig0, Bracket{lo, hi, E_a, E_hi, bound}, sig_f, prev_f, t);
+  return finish(c64, n_c, k, L, N, sig0, br, sig_f, prev_f, t);
 }
 
 }  // namespace inertia

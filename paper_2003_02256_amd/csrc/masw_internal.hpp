@@ -59,7 +59,8 @@ struct alignas(64) Counters {
   uint32_t grid_bad;          // nonzero if the c grid failed validation
   uint32_t coop_stall;        // cooperative waits that reached their bound
   uint32_t tick_exit;         // serving: workgroups that have left their tick (never cleared)
-  uint32_t pad0[12];
+  uint32_t deferred;          // inertia search: wavefronts that left wavelengths to the second launch
+  uint32_t pad0[11];
   unsigned long long useful;  // sum of idx + 1
   unsigned long long sweep;   // sweep evaluations
   unsigned long long check;   // FP64 re-check evaluations
@@ -95,6 +96,7 @@ struct SweepArgs {
   const int32_t* lam_model;
   const int32_t* order;
   int32_t n_items;
+  int32_t n_models;
   int32_t refine;  // 1 = compute c_ref
   double refine_rel;  // refinement bracket width / c_hi
   Counters* counters;

@@ -417,7 +417,7 @@ __global__ __launch_bounds__(kAdmitChunk) void admit_kernel(const AdmitList* __r
 // holds a tick for a long walk.  Returns true once the outputs are written;
 // they equal the walk's.
 template <int G>
-__device__ bool inertia_tick_item(const ItemRef& r, ItemState& st, int budget, SweepShared<G>& sh, WorkCount& wc,
+__device__ __forceinline__ bool inertia_tick_item(const ItemRef& r, ItemState& st, int budget, SweepShared<G>& sh, WorkCount& wc,
                                   const ItemOut& o, Counters* cnt) {
   if (!st.fp64) {
     constexpr int P = 64 * G;
@@ -445,14 +445,14 @@ __device__ bool inertia_tick_item(const ItemRef& r, ItemState& st, int budget, S
         found = inertia::walk(r.c64, r.n_c, r.k64, r.L64, r.N, 1, sig0, &sig_f, &prev_f, t);
       } else if (f == P) {
         // no sampled sign differs: the one-wavefront search from the start
-        found = inertia::search(r.c64, r.n_c, r.k64, r.L64, r.N, -1, &sig_f, &prev_f, t);
+        found = inertia::search(r.c64, r.n_c, r.k64, r.L64, r.N, &sig_f, &prev_f, t);
       } else {
         bool v;
         const int pf = inertia::spread(0, n, f, 1, &v, P);
         const int pb = (f == 1) ? 0 : inertia::spread(0, n, f - 1, 1, &v, P);
         inertia::Bracket br;
-        found = inertia::from_sampled_bound(r.c64, r.n_c, r.k64, r.L64, r.N, 0, false, 0, sig0, pb, pf, &br,
-                                            &sig_f, &prev_f, t);
+        found = inertia::from_sampled_bound(r.c64, r.n_c, r.k64, r.L64, r.N, sig0, pb, pf, &br, &sig_f,
+                                            &prev_f, t);
         if (found == inertia::kLocated)
           found = inertia::finish(r.c64, r.n_c, r.k64, r.L64, r.N, sig0, br, &sig_f, &prev_f, t);
       }
@@ -464,13 +464,10 @@ __device__ bool inertia_tick_item(const ItemRef& r, ItemState& st, int budget, S
           sh.check[2] = t.resume_carry;
         }
       } else {
-        if (found < 0) {
+        if (found < 0)
           write_no_pick(o, MASW_STATUS_NOT_FOUND, lane == 0);
-          wc.useful += (unsigned long long)r.n_c;
-        } else {
-          wc.useful += (unsigned long long)(found + 1);
-          wc.refine += refine_and_write(o, r.c64, r.k64, r.L64, r.N, found, sig_f, prev_f);
-        }
+        else
+          refine_and_write(o, r.c64, r.k64, r.L64, r.N, found, sig_f, prev_f);
         if (lane == 0) sh.check[1] = -1;
       }
     }

@@ -448,6 +448,7 @@ int run_curves(masw_ctx* ctx, const Inputs& in, masw_precision prec, uint32_t fl
   sw.lam_model = p.lam_model;
   sw.order = p.order;
   sw.n_items = int32_t(in.n_lam);
+  sw.n_models = in.n_models;
   sw.refine = (flags & MASW_NO_REFINE) ? 0 : 1;
   sw.refine_rel = ctx->refine_rel;
   sw.counters = p.counters;

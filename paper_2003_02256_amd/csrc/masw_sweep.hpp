@@ -35,12 +35,6 @@ namespace masw {
 // ------------------------------------------------------------ utilities --
 __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
-// v of the previous lane (of lane l - 1, in lane l); lane 0 keeps its own.
-__device__ __forceinline__ int previous_lane(int v) {
-  constexpr int kWaveShr1 = 0x138;  // DPP: a shift by one lane across the wavefront
-  return __builtin_amdgcn_update_dpp(v, v, kWaveShr1, 0xf, 0xf, false);
-}
-
 // What one wavefront has to say about its 64 positions of a round, in one
 // LDS word pair: the sign codes at its first and last positions, the first
 // change inside it plus one (0: none), and the codes at and before that.
@@ -390,7 +384,7 @@ __device__ int coop_sweep(const ItemRef& r, const CoopRef& co, SweepShared<G>& s
 // walked in FP64.  So the split pick is Algorithm 1's pick in FP64 (up to
 // the noise band of the FP64 signs and counts).
 template <int MODE, int G>
-__device__ bool run_item(const ItemRef& r, ItemState& st, int budget, SweepShared<G>& sh, WorkCount& wc,
+__device__ __forceinline__ bool run_item(const ItemRef& r, ItemState& st, int budget, SweepShared<G>& sh, WorkCount& wc,
                          const ItemOut& o, const CoopRef& co, Counters* cnt) {
   constexpr int P = 64 * G;
   const int tid = threadIdx.x;
@@ -572,12 +566,11 @@ __device__ bool run_item(const ItemRef& r, ItemState& st, int budget, SweepShare
   }
   st.done = 1;
 
+  wc.useful += (unsigned long long)(found < 0 ? n_c : found + 1);
   if (found < 0) {
     write_missing<G>(o, MASW_STATUS_NOT_FOUND);
-    wc.useful += (unsigned long long)n_c;
     return true;
   }
-  wc.useful += (unsigned long long)(found + 1);
 
   // Refinement and output by wavefront 0 alone; the others go on to the
   // next barrier.  One wavefront at a time on a SIMD finishes these few
@@ -756,12 +749,12 @@ __device__ void model_finished(const SweepArgs& a, int m, SweepShared<G>& sh, do
 // each to completion; items at queue positions below n_coop run as shared
 // sweeps that workgroups with an empty queue join.  MISFIT: Algorithm 2 fused
 // (model_finished), an instantiation of its own so that the plain sweeps
-// keep their register allocation; it is held to 128 VGPRs (4 wavefronts per
-// SIMD, as the plain FP64 sweeps), spilling a little outside the layer loop.
+// keep their register allocation; it and the plain FP64 sweeps are held to
+// 128 VGPRs (4 wavefronts per SIMD), spilling a little outside the layer loop.
 // The plain split sweeps are held to 96 VGPRs (5 wavefronts per SIMD), which
 // their FP32 loop fits without spilling.
 template <int MODE, int G, bool MISFIT>
-__global__ __launch_bounds__(64 * G) __attribute__((amdgpu_waves_per_eu(MISFIT ? 4 : (MODE == kModeSplit ? 5 : 1))))
+__global__ __launch_bounds__(64 * G) __attribute__((amdgpu_waves_per_eu((MODE == kModeSplit && !MISFIT) ? 5 : 4)))
 void sweep_kernel(SweepArgs a) {
   __shared__ SweepShared<G> sh;
   __shared__ double s_mis[MISFIT ? 256 : 1];  // fused misfit reduction

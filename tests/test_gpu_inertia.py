@@ -291,3 +291,33 @@ def test_random_stress_thirty_configurations(torch_dev, ctx):
                 np.testing.assert_array_equal(y[same], x[same], err_msg=f"{name} seed {seed}: {what}")
         total += len(walk[1])
     print(f"random stress: {total} wavelengths over 30 configurations", flush=True)
+
+
+# Each number of lanes per wavelength (64 up to 2048 wavelengths, 32 up to
+# 4096, 8 up to 32768, then 8 on the persistent grid) at the edges of its
+# range, with models that change inside a wavefront's share, a half-space, an
+# empty and an invalid model, and what the groups leave to a whole wavefront:
+# a half-space slower than the layers, and a grid that starts above the first
+# modes (c_lo 260).
+@pytest.mark.parametrize("c_lo", [50.0, 260.0])
+@pytest.mark.parametrize("n", [1, 9, 2048, 2049, 4096, 4097, 32768, 32769])
+def test_lane_groups_equal_the_walk(torch_dev, ctx, n, c_lo):
+    rng = np.random.Generator(np.random.PCG64(n))
+    models = [WL.two_layer_model(), WL.increasing_profile(rng, 5), WL.increasing_profile(rng, 9),
+              WL.Model(np.zeros(0), np.array([700.0]), np.array([400.0]), np.array([2000.0])),
+              WL.random_model(rng, 4), WL.increasing_profile(rng, 7), WL.increasing_profile(rng, 3)]
+    models[4].beta[-1] = 0.5 * models[4].beta.min()        # slower than every layer
+    models[4].alpha[-1] = 2.0 * models[4].beta[-1]
+    models[5].alpha[1] = 0.5 * models[5].beta[1]           # invalid
+    cut = np.sort(np.r_[0, rng.integers(0, n + 1, len(models) - 2), n])
+    counts = list(np.diff(cut))
+    counts.insert(2, 0)                                    # a model without wavelengths
+    lambdas = [WL.log_spaced(1.0, 60.0, int(k)) if k else np.zeros(0) for k in counts]
+    c = WL.uniform_grid(c_lo, 0.5, 1201)
+    walk = dev_batch(torch_dev, ctx, c, models, lambdas, FP64)
+    got = dev_batch(torch_dev, ctx, c, models, lambdas, FP64, INERTIA)
+    st = ctx.stats()
+    for x, y, what in zip(walk, got, ("C_t", "idx", "status", "c_ref")):
+        np.testing.assert_array_equal(y, x, err_msg=what)
+    assert st["useful_evals"] == int(np.sum(np.where(walk[1] >= 0, walk[1] + 1,
+                                                     np.where(walk[2] == M.MASW_STATUS_NOT_FOUND, len(c), 0))))
