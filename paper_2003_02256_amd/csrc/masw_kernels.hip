@@ -622,7 +622,7 @@ __global__ __launch_bounds__(256) void sign_map_kernel(SignMapArgs a) {
     const LayerRec64* L = a.layers64 + uniform(d.layer_base);
     if (a.logabs) {
       double la;
-      sg = det_sign_logabs<double>(c, k64, L, N, L[N].aux, k64, &la);
+      sg = det_sign_logabs<double>(c, k64, L, N, k64 * L[N].aux, &la);
       a.logabs[o] = la;
     } else {
       sg = det_sign<double, false>(c, k64, L, N, nullptr);
@@ -632,7 +632,7 @@ __global__ __launch_bounds__(256) void sign_map_kernel(SignMapArgs a) {
     const LayerRec64* L64 = a.layers64 + uniform(d.layer_base);
     if (a.logabs) {
       double la;
-      sg = det_sign_logabs<float>(float(c), float(k64), L, N, L64[N].aux, k64, &la);
+      sg = det_sign_logabs<float>(float(c), float(k64), L, N, k64 * L64[N].aux, &la);
       a.logabs[o] = la;
     } else {
       sg = det_sign<float, false>(float(c), float(k64), L, N, nullptr);

@@ -367,15 +367,24 @@ __device__ __forceinline__ int det_sign_parity(T c, T k, const LayerRec<T>* __re
   return sign_code(neg, double(re));
 }
 
-// As det_sign, also returning ln|det K| of the unscaled matrix:
-// sum_j ln|det S_j| + ln|det S_N| + 2(N+1) ln(k mu_ref).
+// As det_sign, also returning ln|det K| of the unscaled matrix,
+// |prod_j det S_j det S_N| (k mu_ref)^(2(N+1)), with km = k mu_ref.  The
+// product is kept as a mantissa and an exponent, each factor taking its
+// (k mu_ref)^2 with it, and one logarithm is taken at the end: a logarithm per
+// layer, and one of k mu_ref, cost about as many instructions again as the
+// elimination (300 wavelengths x 11,501 velocities over 20 layers: 470 us with
+// them, 312 us without).
 template <typename T>
-__device__ __forceinline__ int det_sign_logabs(T c, T k, const LayerRec<T>* __restrict__ L, int N,
-                                               double mu_ref, double k64, double* logabs) {
+__device__ __forceinline__ int det_sign_logabs(T c, T k, const LayerRec<T>* __restrict__ L, int N, double km,
+                                               double* logabs) {
   const T c2 = c * c;
   Block2<T> S{T(0), T(0), T(0)};
   bool neg = false;
-  double acc = 0.0;
+  int ek, ex;
+  const double mk = __builtin_frexp(km, &ek);
+  const double km2 = mk * mk;  // (k mu_ref)^2 = km2 2^(2 ek)
+  double m = 1.0;
+  int e = 2 * (N + 1) * ek;
   LayerRec<T> nxt = load_rec<T>(L, 0);
   for (int j = 0; j < N; ++j) {
     const LayerRec<T> rec = nxt;
@@ -383,13 +392,15 @@ __device__ __forceinline__ int det_sign_logabs(T c, T k, const LayerRec<T>* __re
     const LayerK<T> K = layer_entries<T>(c2, k * rec.h, rec.ia2, rec.ib2, rec.rh, rec.mh);
     const T d = schur_layer<T>(S, K);
     neg ^= (d < T(0));
-    acc += ::log(::fabs(double(d)));
+    m = __builtin_frexp(m * (double(d) * km2), &ex);
+    e += ex;
   }
   const LayerRec<T> hs = nxt;
   T re, im;
   halfspace_det<T>(S, c2, hs.ia2, hs.ib2, hs.mh, &re, &im);
-  acc += ::log(::hypot(double(re), double(im)));
-  *logabs = acc + 2.0 * double(N + 1) * ::log(k64 * mu_ref);
+  const double last = (im == T(0)) ? double(re) : ::hypot(double(re), double(im));
+  m = __builtin_frexp(m * (last * km2), &ex);
+  *logabs = __builtin_fma(double(e + ex), 0.693147180559945309417232, ::log(::fabs(m)));
   return sign_code(neg, double(re));
 }
 
