@@ -159,8 +159,8 @@ __device__ __forceinline__ int count_E(double c, double k, const LayerRec64* __r
   return ok ? s + 2 * P : kEvent;
 }
 
-// The split path's FP64 check of one grid point: det_sign_parity<double>'s
-// sign code and pole parity from the same elimination, and in *E the
+// The split path's FP64 check of one grid point: det_sign's sign code, whether
+// an odd number of the layer denominators are negative (*odd), and in *E the
 // inertia of its pivots, s(c), or kEvent where a pivot is zero or not finite
 // or c is at or above the half-space's S velocity.  E(c) = s(c) when
 // *poles_bounded (every layer's P_j is zero by the energy bound); otherwise

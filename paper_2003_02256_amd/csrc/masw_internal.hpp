@@ -31,12 +31,12 @@ struct alignas(8 * sizeof(T)) LayerRec {
   T ia2;  // 1 / alpha^2
   T ib2;  // 1 / beta^2
   T rh;   // rho / mu_ref
-  T mh;   // mu / mu_ref
+  T mh;   // mu / mu_ref; in the FP32 records of staged searches, whose mu
+          // nothing reads, the depth of the layer's bottom (m) for the work-order key
   T h;    // thickness (0 for the half-space record)
-  T aux;   // half-space record: mu_ref (Pa); 0 otherwise
-  T zb;    // depth of the layer's bottom (m), for the work-order key of the
-           // batch staging; 0 in served requests, which are not reordered
-  T pad2;
+  T aux;  // layer j: rho_j / rho_{j+1}; half-space record: mu_ref (Pa)
+  T idr;  // layer j: rho_{j+1} / rho_j; half-space record: 0
+  T kap;  // layer j: 2 (mu_{j+1} - mu_j) / rho_{j+1}; half-space record: 0 (masw_secular.hpp)
 };
 using LayerRec64 = LayerRec<double>;
 using LayerRec32 = LayerRec<float>;
@@ -184,6 +184,7 @@ struct PrepArgs {
   uint8_t* lam_bucket;
   int32_t* order;
   int32_t n_lam;
+  bool map;  // staged for the sign map, whose FP32 records keep mu
   Counters* counters;
   uint32_t* grid_flags;  // [ceil(n_c / kPrepThreads)] 1 where a block of the grid failed its checks
   int32_t* model_left;   // fused misfit: [n_models] set to each model's wavelength count (else null)

@@ -12,6 +12,7 @@
 #include "masw_internal.hpp"
 #include "masw_math.hpp"
 #include "masw_pick.hpp"
+#include "masw_secular.hpp"
 #include "masw_sweep.hpp"
 
 namespace masw {
@@ -108,19 +109,21 @@ __device__ void build_model(const PrepArgs& a, int m, int single_N, int single_W
     r.rh = rh / mu_ref;
     r.mh = rh * be * be / mu_ref;
     r.h = (j < N) ? a.h[lo + j] : 0.0;
-    r.aux = (j == N) ? mu_ref : 0.0;
-    r.zb = z;
-    r.pad2 = 0.0;
+    secular::Interface f{mu_ref, 0.0, 0.0};
+    if (j < N) f = secular::interface_of(rh, be, a.rho[rec0 + j + 1], a.beta[rec0 + j + 1]);
+    r.aux = f.dr;
+    r.idr = f.idr;
+    r.kap = f.kap;
     a.layers64[rec0 + j] = r;
     LayerRec32 q;
     q.ia2 = float(r.ia2);
     q.ib2 = float(r.ib2);
     q.rh = float(r.rh);
-    q.mh = float(r.mh);
+    q.mh = float(a.map ? r.mh : z);
     q.h = float(r.h);
-    q.aux = float(mu_ref);
-    q.zb = float(z);
-    q.pad2 = 0.0f;
+    q.aux = float(f.dr);
+    q.idr = float(f.idr);
+    q.kap = float(f.kap);
     a.layers32[rec0 + j] = q;
   }
 }
@@ -217,11 +220,12 @@ __device__ void stage_lambdas(const PrepArgs& a, int bad, LambdaShared& ls) {
     key = kBuckets - 1;
     if (ok) {
       const LayerRec64* L = a.layers64 + d.layer_base;
+      const LayerRec32* L32 = a.layers32 + d.layer_base;
       int lo = 0, hi = d.n_layers;  // first layer whose bottom reaches lambda / 3
       const double z3 = lam * (1.0 / 3.0);
       while (lo < hi) {
         const int mid = (lo + hi) >> 1;
-        if (L[mid].zb < z3) lo = mid + 1; else hi = mid;
+        if (double(L32[mid].mh) < z3) lo = mid + 1; else hi = mid;
       }
       const double c_est = 0.9 / ::sqrt(L[lo].ib2);
       double pos = 0.0;  // interpolated grid index of c_est
@@ -383,8 +387,11 @@ __global__ __launch_bounds__(kAdmitChunk) void admit_kernel(const AdmitList* __r
       r.rh = rh / mu_ref;
       r.mh = rh * be * be / mu_ref;
       r.h = (j < N) ? h[j] : 0.0;
-      r.aux = (j == N) ? mu_ref : 0.0;
-      r.zb = r.pad2 = 0.0;
+      secular::Interface f{mu_ref, 0.0, 0.0};
+      if (j < N) f = secular::interface_of(rh, be, rho[j + 1], beta[j + 1]);
+      r.aux = f.dr;
+      r.idr = f.idr;
+      r.kap = f.kap;
       d.L64[j] = r;
       LayerRec32 q;
       q.ia2 = float(r.ia2);
@@ -392,8 +399,9 @@ __global__ __launch_bounds__(kAdmitChunk) void admit_kernel(const AdmitList* __r
       q.rh = float(r.rh);
       q.mh = float(r.mh);
       q.h = float(r.h);
-      q.aux = float(mu_ref);
-      q.zb = q.pad2 = 0.0f;
+      q.aux = float(f.dr);
+      q.idr = float(f.idr);
+      q.kap = float(f.kap);
       d.L32[j] = q;
     }
   }

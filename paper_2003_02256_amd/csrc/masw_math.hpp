@@ -52,6 +52,11 @@ __device__ __forceinline__ float fma_(float a, float b, float c) {
   return __builtin_fmaf(a, b, c);
 }
 
+__device__ __forceinline__ double frexp_(double x, int* e) { return __builtin_frexp(x, e); }
+__device__ __forceinline__ float frexp_(float x, int* e) { return __builtin_frexpf(x, e); }
+__device__ __forceinline__ double ldexp_(double x, int e) { return __builtin_ldexp(x, e); }
+__device__ __forceinline__ float ldexp_(float x, int e) { return __builtin_ldexpf(x, e); }
+
 template <typename T>
 __device__ __forceinline__ T sqrt_(T x) {
   return __builtin_sqrt(x);
@@ -273,7 +278,7 @@ __device__ __forceinline__ LayerRec<T> load_rec(const LayerRec<T>* L, int j) {
     r.h = p->h;
     r.aux = p->aux;
   }
-  r.zb = r.pad2 = T(0);
+  r.idr = r.kap = T(0);  // (secular::load_layer reads them)
   return r;
 }
 
@@ -341,30 +346,6 @@ __device__ __forceinline__ int det_sign_value(double c, double k, const LayerRec
   *mant = __builtin_frexp(m * re, &ex);
   *expo = e + ex;
   return sign_code(neg, re);
-}
-
-// As det_sign, also returning in *odd whether an odd number of the layer
-// denominators D_j are negative.  That parity flips where c crosses a pole of
-// det K (one D_j changes sign there).
-template <typename T>
-__device__ __forceinline__ int det_sign_parity(T c, T k, const LayerRec<T>* __restrict__ L, int N, int* odd) {
-  const T c2 = c * c;
-  Block2<T> S{T(0), T(0), T(0)};
-  bool neg = false, par = false;
-  LayerRec<T> nxt = load_rec<T>(L, 0);
-  for (int j = 0; j < N; ++j) {
-    const LayerRec<T> rec = nxt;
-    nxt = load_rec<T>(L, j + 1);
-    const LayerK<T> K = layer_entries<T>(c2, k * rec.h, rec.ia2, rec.ib2, rec.rh, rec.mh);
-    par ^= (K.gD < T(0));
-    const T d = schur_layer<T>(S, K);
-    neg ^= (d < T(0));
-  }
-  const LayerRec<T> hs = nxt;
-  T re, im;
-  halfspace_det<T>(S, c2, hs.ia2, hs.ib2, hs.mh, &re, &im);
-  *odd = par ? 1 : 0;
-  return sign_code(neg, double(re));
 }
 
 // As det_sign, also returning ln|det K| of the unscaled matrix,

@@ -189,14 +189,22 @@ struct Refine8 {
 // 1/det K at a pole) between the new bracket's ends estimates the root, and
 // lanes 1..62 are placed 0.9 tol apart around the estimate.
 // Returns the determinant evaluations made (8 or 64 a round).
+// With `confirm` the signs are a sweep's (masw_secular.hpp), and the
+// determinant's own at the two grid points, which the first round evaluates,
+// have the last word: kUnconfirmed is added, and nothing written, where they
+// show no change.
+constexpr unsigned long long kUnconfirmed = 1ull << 63;
 __device__ __forceinline__ unsigned long long refine_and_write(const ItemOut& o, const double* c64, double k64,
                                                                const LayerRec64* L64, int N, int found, int sig_f,
-                                                               int prev_f) {
+                                                               int prev_f, bool confirm = false) {
   constexpr int kUniform64 = 3, kWindow64 = 4;  // stages of the multisection
   const int lane = threadIdx.x & 63;
   unsigned long long evals = 0;
   int status = MASW_STATUS_FOUND;
-  if (sig_f == kNaNSign || prev_f == kNaNSign) status = MASW_STATUS_NAN;
+  if (sig_f == kNaNSign || prev_f == kNaNSign) {
+    if (confirm) return kUnconfirmed;
+    status = MASW_STATUS_NAN;
+  }
   double c_ref = __builtin_nan("");
   if (status == MASW_STATUS_FOUND) {
     Refine8<true> r;
@@ -224,6 +232,10 @@ __device__ __forceinline__ unsigned long long refine_and_write(const ItemOut& o,
       if (r.stage < kUniform64) {
         evals += 8ull;
         if (k == 0) {
+          if (confirm) {
+            const int s_lo = from_lane<true>(sg, 0), s_hi = from_lane<true>(sg, 7);
+            if (s_lo == s_hi || s_lo == kNaNSign || s_hi == kNaNSign) return evals + kUnconfirmed;
+          }
           const uint64_t dm_lo = (uint64_t(uint32_t(from_lane<true>(int(uint32_t(dm >> 32)), 0))) << 32) |
                                  uint32_t(from_lane<true>(int(uint32_t(dm)), 0));
           const unsigned long long other = __ballot(dm != dm_lo);

@@ -821,6 +821,7 @@ int masw_sign_map(masw_ctx* ctx, const double* c_test, int32_t n_c, const double
   p.n_models = 1;
   p.n_c = n_c;
   p.n_lam = n_lambda;
+  p.map = true;
   int8_t* sig_dst = sigma;
   double* log_dst = log_abs_det;
   if (dev) {

@@ -29,6 +29,7 @@
 #include "masw_internal.hpp"
 #include "masw_math.hpp"
 #include "masw_pick.hpp"
+#include "masw_secular.hpp"
 
 namespace masw {
 
@@ -101,6 +102,12 @@ __device__ __forceinline__ int round_first_change(int sg, int prev0, WaveSum* su
   return w * 64 + __builtin_amdgcn_readlane(edge ? 0 : change - 1, w);
 }
 
+// The determinant's sign code of a grid point in the FP64 sweep.
+__device__ __forceinline__ int sweep_sign64(double c, double k, const LayerRec64* L, int N) {
+  int odd;
+  return secular::sign<double>(c, k, L, N, &odd);
+}
+
 // Sweep code of a grid point in the FP32 sweep: the determinant's sign code,
 // plus 4 when an odd number of layer denominators are negative.  The parity
 // flips where c crosses a pole of det K, so a pole crossing is a candidate
@@ -109,7 +116,7 @@ __device__ __forceinline__ int round_first_change(int sg, int prev0, WaveSum* su
 // which FP32 would otherwise see the same sign).
 __device__ __forceinline__ int sweep_code32(float c, float k, const LayerRec32* L, int N) {
   int odd;
-  const int sg = det_sign_parity<float>(c, k, L, N, &odd);
+  const int sg = secular::sign<float>(c, k, L, N, &odd);
   return sg + 4 * odd;
 }
 
@@ -226,7 +233,7 @@ __device__ __forceinline__ int eval_round(const ItemRef& r, int rd, SweepShared<
   int sg = kNoSign;
   if (i < sweep_len<T>(r)) {
     if constexpr (sizeof(T) == 8)
-      sg = det_sign<double, false>(r.c64[i], r.k64, r.L64, r.N, nullptr);
+      sg = sweep_sign64(r.c64[i], r.k64, r.L64, r.N);
     else
       sg = sweep_code32(c32_at(r, i), float(r.k64), r.L32, r.N);
   }
@@ -555,7 +562,7 @@ __device__ __forceinline__ bool run_item(const ItemRef& r, ItemState& st, int bu
       }
       ++rounds;
       const int i = base + tid;
-      const int sg = (i < n_c) ? det_sign<double, false>(r.c64[i], r.k64, r.L64, r.N, nullptr) : kNoSign;
+      const int sg = (i < n_c) ? sweep_sign64(r.c64[i], r.k64, r.L64, r.N) : kNoSign;
       const int f = round_first_change<G>(sg, carry, sh.sum[rounds & 1], &carry, &sig_f, &prev_f);
       wc.sweep += (unsigned long long)min(P, n_c - base);
       if (f >= 0) {
@@ -575,7 +582,24 @@ __device__ __forceinline__ bool run_item(const ItemRef& r, ItemState& st, int bu
   // Refinement and output by wavefront 0 alone; the others go on to the
   // next barrier.  One wavefront at a time on a SIMD finishes these few
   // rounds sooner than the whole group sharing the SIMDs would.
-  if (wave == 0) wc.refine += refine_and_write(o, r.c64, r.k64, r.L64, r.N, found, sig_f, prev_f);
+  if (wave == 0) {
+    bool confirm = fp64;  // (the split path's window has the determinant's own signs)
+    for (;;) {
+      const unsigned long long n = refine_and_write(o, r.c64, r.k64, r.L64, r.N, found, sig_f, prev_f, confirm);
+      wc.refine += n & ~kUnconfirmed;
+      if (!(n & kUnconfirmed)) break;
+      // A sign within rounding of the change (one pick in 10^7) or no number:
+      // Algorithm 1 by the elimination, by this wavefront alone.
+      inertia::Tally t;
+      found = inertia::walk(r.c64, n_c, r.k64, r.L64, r.N, 0, kNoSign, &sig_f, &prev_f, t);
+      wc.sweep += t.scan;
+      if (found < 0) {
+        write_no_pick(o, MASW_STATUS_NOT_FOUND, lane == 0);
+        break;
+      }
+      confirm = false;
+    }
+  }
   return true;
 }
 
@@ -847,9 +871,11 @@ __global__ __launch_bounds__(64 * kFusedG) void fused_sweep_kernel(SweepArgs a) 
     r.rh = rh / mu_ref;
     r.mh = rh * be * be / mu_ref;
     r.h = h;
-    r.aux = (j == N) ? mu_ref : 0.0;
-    r.zb = 0.0;  // only the batch staging's work order reads it
-    r.pad2 = 0.0;
+    secular::Interface f{mu_ref, 0.0, 0.0};
+    if (j < N) f = secular::interface_of(rh, be, a.f_rho[j + 1], a.f_beta[j + 1]);
+    r.aux = f.dr;
+    r.idr = f.idr;
+    r.kap = f.kap;
     L64[j] = r;
     LayerRec32 q;
     q.ia2 = float(r.ia2);
@@ -857,9 +883,9 @@ __global__ __launch_bounds__(64 * kFusedG) void fused_sweep_kernel(SweepArgs a) 
     q.rh = float(r.rh);
     q.mh = float(r.mh);
     q.h = float(r.h);
-    q.aux = float(mu_ref);
-    q.zb = 0.0f;
-    q.pad2 = 0.0f;
+    q.aux = float(f.dr);
+    q.idr = float(f.idr);
+    q.kap = float(f.kap);
     L32[j] = q;
   }
   // the grid: finite, > 0, strictly increasing (the staging's checks), and
