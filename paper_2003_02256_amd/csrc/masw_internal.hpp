@@ -59,8 +59,10 @@ struct alignas(64) Counters {
   uint32_t grid_bad;          // nonzero if the c grid failed validation
   uint32_t coop_stall;        // cooperative waits that reached their bound
   uint32_t tick_exit;         // serving: workgroups that have left their tick (never cleared)
-  uint32_t deferred;          // inertia search: wavefronts that left wavelengths to the second launch
-  uint32_t pad0[11];
+  uint32_t deferred;          // inertia search: wavefronts that left wavelengths to the second launch;
+                              // staged picks: wavelengths left to the last launch
+  uint32_t rest_head;         // staged picks: the next of them
+  uint32_t pad0[10];
   unsigned long long useful;  // sum of idx + 1
   unsigned long long sweep;   // sweep evaluations
   unsigned long long check;   // FP64 re-check evaluations
@@ -94,7 +96,7 @@ struct SweepArgs {
   const float* c32;
   const double* lam_k;
   const int32_t* lam_model;
-  const int32_t* order;
+  int32_t* order;  // (staged picks: after the sweep, the wavelengths left to the last launch)
   int32_t n_items;
   int32_t n_models;
   int32_t refine;  // 1 = compute c_ref

@@ -1,0 +1,243 @@
+// The walk and the split path on many wavelengths: sweep, then picks.
+//
+// A sweeping wavefront (masw_sweep.hpp) that checks and refines its own pick
+// eliminates K at 64 positions for the split path's check and, twice, at the
+// eight points of the refinement with all its 64 lanes.  Over 1.12 M
+// wavelengths of 16.5 layers that was 8 of the walk's 160 ms and 13 of the
+// split path's 83.  Where there are items enough to keep every SIMD busy
+// without the deepest of them deciding the time, the work is three launches
+// instead:
+//   first_change_kernel: the sweep alone, one wavefront per item of the work
+//       order.  Its candidate goes to out_idx.  Without the eliminations it
+//       needs few registers (FP32: eight wavefronts per SIMD).
+//   pick_kernel: eight lanes per wavelength, eight wavelengths of one model
+//       at a time.  Split: the FP64 points from four before the candidate to
+//       three after it; the first one with E != 0 whose predecessor has E = 0
+//       is the pick if sign(det K) changes there, since E = 0 proves that
+//       there is no earlier change (masw_inertia.hpp).  Then, and on the walk
+//       at once, the refinement by eight points a round (Refine8), whose
+//       first round has K's own signs at the pick's two grid points.
+//   pick_rest_kernel: the others (no change found in FP32, a candidate that
+//       the eight points do not settle, a pole in the step or several changes,
+//       a sign within rounding of the change), by a whole wavefront each, as
+//       the one-launch sweep does them from the candidate on.
+// Between the launches out_idx holds the candidate, or kDeferredIdx with the
+// candidate (-1: none) in out_status.  Indices, statuses and roots are those
+// of the one-launch sweep: the same eliminations at the same points decide.
+// The 1.12 M wavelengths (19,001 velocities): 160 -> 151 ms, split 83 -> 69;
+// before the sweeps' sign function, 211 and 98.
+#define MASW_COEFF_POLICY 1
+#include "masw_inertia_kernel.hpp"
+#include "masw_sweep.hpp"
+
+namespace masw {
+namespace {
+
+// Sweeping wavefronts per SIMD.  Measured on the 4096 models above, the whole
+// call (ms): FP64 with 4 to 8 of them 154.1, 152.0, 151.2, 153.4, 153.6; FP32
+// 82.3, 74.3, 70.2, 68.3, 69.7 (one launch, 4 and 5: 160.3 and 82.7).
+template <int MODE>
+constexpr int kSweepWaves = MODE == kModeSplit ? 7 : 6;
+
+template <int MODE>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kSweepWaves<MODE>)))
+void first_change_kernel(SweepArgs a) {
+  const int lane = threadIdx.x;
+  WorkCount wc;
+  stamp_start(a.tstamp, 1);
+  for (unsigned it = blockIdx.x;;) {
+    if (it >= unsigned(a.n_items)) break;
+    int g;
+    const ItemRef r = item_ref(a, int(it), &g);
+    if (int(it) < a.prio_hi) __builtin_amdgcn_s_setprio(2);
+    else if (int(it) < a.prio_mid) __builtin_amdgcn_s_setprio(1);
+    else __builtin_amdgcn_s_setprio(0);
+    const ItemOut o = item_out(a, g);
+    if (!(r.k64 == r.k64)) {  // invalid model, grid or wavelength
+      write_no_pick(o, MASW_STATUS_INVALID, lane == 0);
+    } else {
+      const int n = MODE == kModeFP64 ? r.n_c : r.n_real;
+      const float k32 = float(r.k64);
+      int carry = kNoSign, found = -1, sig_f, prev_f;
+      for (int base = 0; base < n; base += 64) {
+        const int i = base + lane;
+        int sg = kNoSign;
+        if (i < n) {
+          if constexpr (MODE == kModeFP64) sg = sweep_sign64(r.c64[i], r.k64, r.L64, r.N);
+          else sg = sweep_code32(r.c32[i], k32, r.L32, r.N);
+        }
+        const int f = round_first_change<1>(sg, carry, nullptr, &carry, &sig_f, &prev_f);
+        wc.sweep += (unsigned long long)min(64, n - base);
+        if (f >= 0) {
+          found = base + f;
+          break;
+        }
+      }
+      if (MODE == kModeFP64 && found < 0) {
+        write_no_pick(o, MASW_STATUS_NOT_FOUND, lane == 0);
+        wc.useful += (unsigned long long)n;
+      } else if (lane == 0) {
+        *o.idx = found < 0 ? kDeferredIdx : found;
+        *o.status = found;
+      }
+    }
+    unsigned q = 0;
+    if (lane == 0) q = atomicAdd(&a.counters->queue_head, 1u);
+    it = gridDim.x + unsigned(uniform(int(q)));
+  }
+  __builtin_amdgcn_s_setprio(0);
+  flush_counts(a.counters, a.wg_counts, wc);
+  stamp_end(a.tstamp);
+}
+
+// The picks of the wavelengths [begin, end) of one model, 64 / 8 at a time,
+// each eight lanes a run of consecutive ones.  Per-lane variables are the
+// same in a group's lanes.
+template <int MODE>
+__device__ __forceinline__ void run_picks(const SweepArgs& a, int begin, int end, const ModelDesc& d, WorkCount& wc) {
+  const int lane = threadIdx.x & 63, sub = lane & 7, base = lane & ~7;
+  const int N = uniform(d.n_layers), n_c = uniform(d.n_c);
+  const double* c64 = a.c64 + uniform(d.c_base);
+  const LayerRec64* L = a.layers64 + uniform(d.layer_base);
+  const int per = (end - begin + 7) / 8;
+  int g = begin + (lane >> 3) * per;
+  const int g_end = min(g + per, end);
+  auto in_group = [&](bool p) -> unsigned { return unsigned(__ballot(p) >> base) & 0xffu; };
+  double k = 1.0;
+  int at = 0, first = 0;  // candidate, then pick; first of the points of its check
+  bool live = false, check = false;
+  Refine8<false> r;
+  r.init(0.0, 0.0, 0.0);
+  for (;;) {
+    while (!live && g < g_end) {  // the group's next candidate
+      at = a.out_idx[g];
+      if (at < 1) {
+        ++g;
+        continue;
+      }
+      k = a.lam_k[g];
+      live = true;
+      check = MODE == kModeSplit;
+      if (check) {
+        first = max(0, min(at - 4, n_c - 8));
+      } else {
+        r.init(c64[at - 1], c64[at], a.refine_rel);
+      }
+    }
+    if (__ballot(live) == 0ull) break;
+    const double c = check ? c64[min(first + sub, n_c - 1)] : r.point(sub);
+    const Point v = eval_point(c, k, L, N);
+    const int sg_prev = previous_lane(v.sg);
+    const unsigned above = in_group(!v.zero), pole = in_group(v.pole);
+    const unsigned changes = in_group(sub > 0 && v.sg != sg_prev), nan = in_group(v.sg == kNaNSign);
+    wc.check += __popcll(__ballot(live && check));
+    wc.refine += __popcll(__ballot(live && !check));
+    bool rest = false, done = false;
+    if (live && check) {
+      const int f = above ? __ffs(int(above)) - 1 : 0;  // first point with E != 0
+      const double c_lo = from_lane<false>(c, base + max(f - 1, 0)), c_hi = from_lane<false>(c, base + f);
+      at = f > 0 ? first + f : at;
+      rest = f == 0 || !(changes >> f & 1u) || (nan >> f & 1u);
+      r.init(c_lo, c_hi, a.refine_rel);
+      check = false;
+    } else if (live) {
+      const int s_lo = from_lane<false>(v.sg, base), s_hi = from_lane<false>(v.sg, base + 7);
+      if (r.stage == 0 && r.round == 0 && (pole != 0u || nan != 0u || s_lo == s_hi || __popc(changes) > 1))
+        rest = true;
+      else
+        done = r.update(c, v.sg, v.m, v.e, base) || !a.refine;
+    }
+    if (rest || done) {
+      const ItemOut o = item_out(a, g);
+      if (sub == 0) {
+        *o.idx = rest ? kDeferredIdx : at;
+        *o.status = rest ? at : MASW_STATUS_FOUND;
+        if (done) {
+          *o.ct = c64[at];
+          if (o.cref) *o.cref = o.refine ? 0.5 * (r.lo + r.hi) : __builtin_nan("");
+          wc.useful += (unsigned long long)(at + 1);
+        }
+      }
+      live = false;
+      check = false;
+      ++g;
+    }
+  }
+}
+
+template <int MODE>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void pick_kernel(SweepArgs a, int chunk) {
+  WorkCount wc;
+  const int64_t n_waves = int64_t(gridDim.x) * 4;
+  for (int64_t run = int64_t(blockIdx.x) * 4 + uniform(threadIdx.x >> 6); run * chunk < a.n_items; run += n_waves) {
+    const int begin = int(run * chunk), last = int(std::min<int64_t>((run + 1) * chunk, a.n_items));
+    for (int g = begin; g < last;) {
+      const ModelDesc d = a.models[uniform(a.lam_model[g])];
+      const int stop = min(last, uniform(d.lam_base + d.n_lam));
+      run_picks<MODE>(a, g, stop, d, wc);
+      g = stop;
+    }
+    // The run's wavelengths that are left to the last launch, by one atomic:
+    // the work order, which the sweep has been through, becomes their list.
+    __threadfence();
+    const int lane = threadIdx.x & 63;
+    const bool left = begin + lane < last && ld_agent(a.out_idx + begin + lane) == kDeferredIdx;
+    const unsigned long long all = __ballot(left);
+    if (all != 0ull) {
+      unsigned at = 0;
+      if (lane == 0) at = atomicAdd(&a.counters->deferred, unsigned(__popcll(all)));
+      at = unsigned(uniform(int(at))) + unsigned(__popcll(all & ((1ull << lane) - 1ull)));
+      if (left) a.order[at] = begin + lane;
+    }
+  }
+  wc.useful = inertia::wave_sum(wc.useful);
+  if ((threadIdx.x & 63) == 0) {
+    if (wc.check) atomicAdd(&a.counters->check, wc.check);
+    atomicAdd(&a.counters->refine, wc.refine);
+    atomicAdd(&a.counters->useful, wc.useful);
+  }
+  stamp_end(a.tstamp);
+}
+
+template <int MODE>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void pick_rest_kernel(SweepArgs a) {
+  __shared__ SweepShared<1> sh;
+  const unsigned n = a.counters->deferred;
+  if (n == 0u) return;
+  WorkCount wc;
+  for (;;) {
+    unsigned i = 0;
+    if (threadIdx.x == 0) i = atomicAdd(&a.counters->rest_head, 1u);
+    i = unsigned(uniform(int(i)));
+    if (i >= n) break;
+    const int g = uniform(a.order[i]);
+    const ItemRef r = item_of(a, g);
+    const ItemOut o = item_out(a, g);
+    ItemState st = item_state_init();
+    run_item<MODE, 1, true>(r, st, 0x7fffffff, sh, wc, o, kNoCoop, a.counters, uniform(*o.status));
+  }
+  if (wc.refine + wc.check + wc.sweep != 0ull) flush_counts(a.counters, nullptr, wc);
+  stamp_end(a.tstamp);
+}
+
+template <int MODE>
+hipError_t launch(int cus, hipStream_t s, const SweepArgs& a, int* blocks_out) {
+  // wavelengths a wavefront takes at a time: as launch_inertia's runs
+  const int chunk = int(std::max<int64_t>(8, std::min<int64_t>(64, int64_t(a.n_items) / (int64_t(cus) * 32) / 8 * 8)));
+  const int64_t runs = (int64_t(a.n_items) + chunk - 1) / chunk;
+  const int64_t blocks = std::min<int64_t>(a.n_items, int64_t(cus) * 4 * kSweepWaves<MODE>);
+  *blocks_out = int(blocks);
+  hipLaunchKernelGGL(first_change_kernel<MODE>, dim3(unsigned(blocks)), dim3(64), 0, s, a);
+  hipLaunchKernelGGL(pick_kernel<MODE>, dim3(unsigned(std::min<int64_t>((runs + 3) / 4, int64_t(cus) * 4))), dim3(256),
+                     0, s, a, chunk);
+  hipLaunchKernelGGL(pick_rest_kernel<MODE>, dim3(unsigned(cus) * 16), dim3(64), 0, s, a);
+  return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_staged_picks(int mode, int cus, hipStream_t s, const SweepArgs& a, int* blocks_out) {
+  return mode == kModeFP64 ? launch<kModeFP64>(cus, s, a, blocks_out) : launch<kModeSplit>(cus, s, a, blocks_out);
+}
+
+}  // namespace masw

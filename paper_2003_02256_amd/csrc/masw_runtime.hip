@@ -411,6 +411,16 @@ int run_curves(masw_ctx* ctx, const Inputs& in, masw_precision prec, uint32_t fl
     sw.f_n_c = in.n_c;
   }
 
+  // Sweep and picks as launches of their own (masw_picks.hip) where there are
+  // items enough that their throughput decides, not the deepest of them or the
+  // second launch's latency.  One launch against three (ms): 17,281
+  // wavelengths x 9,501 velocities 1.48 and 1.49 (split 1.09 and 1.09), 36,281
+  // 2.78 and 2.67 (1.60 and 1.34), 69,443 5.43 and 5.20 (3.10 and 2.43); x
+  // 19,001 velocities 36,469 5.14 and 5.23 (2.66 and 2.33), 70,340 10.70 and
+  // 10.67 (5.55 and 4.92).
+  const bool staged = !inertia && !in.misfit && G == 1 && ci.n_coop == 0 &&
+                      int64_t(in.n_lam) > 48 * 4 * int64_t(ctx->cus);
+
   // timed (a slot of the stamp ring) unless no-alloc or without a sweep
   masw_ctx::TimingSlot* T = nullptr;
   const int ts = ctx->tslot_next;
@@ -462,7 +472,9 @@ int run_curves(masw_ctx* ctx, const Inputs& in, masw_precision prec, uint32_t fl
   if (fused)
     MASW_HIP(launch_fused(mode, blocks, s, sw));
   else if (in.n_lam > 0)
-    MASW_HIP(inertia ? launch_inertia(sw, ctx->cus, s, &blocks) : launch_sweep(mode, G, blocks, s, sw));
+    MASW_HIP(inertia  ? launch_inertia(sw, ctx->cus, s, &blocks)
+             : staged ? launch_staged_picks(mode, ctx->cus, s, sw, &blocks)
+                      : launch_sweep(mode, G, blocks, s, sw));
   if (T && T->events) MASW_HIP(hipEventRecord(T->ev[2], s));
   if (in.misfit && inertia)
     MASW_HIP(launch_misfit(in.n_models, p.lambda_off, sw.out_ct, c_e_dev, misfit_dev, s));

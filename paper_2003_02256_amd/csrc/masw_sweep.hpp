@@ -390,9 +390,11 @@ __device__ int coop_sweep(const ItemRef& r, const CoopRef& co, SweepShared<G>& s
 // from the segment's origin; the grid above the half-space's S velocity is
 // walked in FP64.  So the split pick is Algorithm 1's pick in FP64 (up to
 // the noise band of the FP64 signs and counts).
-template <int MODE, int G>
+// SWEPT: the first sweep has been made, by another launch; its candidate is
+// `swept` (-1: none).
+template <int MODE, int G, bool SWEPT = false>
 __device__ __forceinline__ bool run_item(const ItemRef& r, ItemState& st, int budget, SweepShared<G>& sh, WorkCount& wc,
-                         const ItemOut& o, const CoopRef& co, Counters* cnt) {
+                         const ItemOut& o, const CoopRef& co, Counters* cnt, int swept = 0) {
   constexpr int P = 64 * G;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -410,7 +412,7 @@ __device__ __forceinline__ bool run_item(const ItemRef& r, ItemState& st, int bu
     const float k32 = float(r.k64);
     const int n32 = r.n_real;
     int seg_start = st.seg_start, seg_carry = st.seg_carry;
-    bool shared = co.ci != nullptr;  // the first FP32 pass is a shared sweep
+    bool shared = SWEPT || co.ci != nullptr;  // the first FP32 pass is a shared sweep, or made
     for (;;) {
       // FP32 sweep for a candidate, from `start` (inside the segment that
       // began at seg_start, whose predecessor's FP64 sign is seg_carry).
@@ -418,7 +420,8 @@ __device__ __forceinline__ bool run_item(const ItemRef& r, ItemState& st, int bu
       if (shared) {
         shared = false;
         int s_c = 0, p_c = 0;
-        cand = coop_sweep<float, G>(r, co, sh, wc, cnt, &s_c, &p_c);
+        if constexpr (SWEPT) cand = swept;
+        else cand = coop_sweep<float, G>(r, co, sh, wc, cnt, &s_c, &p_c);
         if (cand == kCoopStall) {
           st.done = 1;
           write_missing<G>(o, MASW_STATUS_INVALID);
@@ -546,7 +549,9 @@ __device__ __forceinline__ bool run_item(const ItemRef& r, ItemState& st, int bu
       }
     }
   }
-  if (fp64 && MODE == kModeFP64 && co.ci) {
+  if constexpr (SWEPT && MODE == kModeFP64) {
+    found = swept;
+  } else if (fp64 && MODE == kModeFP64 && co.ci) {
     found = coop_sweep<double, G>(r, co, sh, wc, cnt, &sig_f, &prev_f);
     if (found == kCoopStall) {
       st.done = 1;
@@ -624,10 +629,8 @@ __device__ __forceinline__ void flush_counts(Counters* c, unsigned long long* wg
   if (wc.helper) atomicAdd(&c->helper, wc.helper);
 }
 
-// The uniform description of the item at queue position `it`; *g_out is its
-// wavelength and *m_out (if given) its model.
-__device__ __forceinline__ ItemRef item_ref(const SweepArgs& a, int it, int* g_out, int* m_out = nullptr) {
-  const int g = uniform(a.order[it]);
+// The uniform description of wavelength g; *m_out (if given) is its model.
+__device__ __forceinline__ ItemRef item_of(const SweepArgs& a, int g, int* m_out = nullptr) {
   const int m = uniform(a.lam_model[g]);
   if (m_out) *m_out = m;
   const ModelDesc d = a.models[m];
@@ -640,8 +643,15 @@ __device__ __forceinline__ ItemRef item_ref(const SweepArgs& a, int it, int* g_o
   r.c32 = a.c32 + uniform(d.c_base);
   r.L64 = a.layers64 + uniform(d.layer_base);
   r.L32 = a.layers32 + uniform(d.layer_base);
-  *g_out = g;
   return r;
+}
+
+// The uniform description of the item at queue position `it`; *g_out is its
+// wavelength and *m_out (if given) its model.
+__device__ __forceinline__ ItemRef item_ref(const SweepArgs& a, int it, int* g_out, int* m_out = nullptr) {
+  const int g = uniform(a.order[it]);
+  *g_out = g;
+  return item_of(a, g, m_out);
 }
 
 // A workgroup that finds the queue empty joins the shared sweeps still open:

@@ -87,3 +87,39 @@ def test_a_pick_is_a_change_of_the_determinant(torch_dev, ctx, ulps):
             assert np.all(s == s[0])
             continue
         assert s[idx[0]] != s[idx[0] - 1] and ct[0] == c[idx[0]]
+
+
+@pytest.mark.parametrize("flags", [0, M.MASW_NO_REFINE])
+@pytest.mark.parametrize("prec", [M.MASW_PREC_FP64, M.MASW_PREC_SPLIT])
+@pytest.mark.parametrize("extra", [1, 700])
+def test_sweep_and_picks_in_launches_of_their_own(torch_dev, ctx, extra, prec, flags):
+    # just above the item count (48 per SIMD) from which the sweep, the picks
+    # and the picks that eight lanes do not settle are separate launches:
+    # outputs equal those of the same items in batches below it, bit for bit.
+    # The models have poles, changes below the grid, no change at all and
+    # modes in the grid's last steps; some are invalid.
+    torch, dev = torch_dev
+    n = 48 * 4 * torch.cuda.get_device_properties(dev).multi_processor_count + extra
+    rng = np.random.Generator(np.random.PCG64(77 + extra))
+    models, lambdas, left = [], [], n
+    while left > 0:
+        i = len(models)
+        m = WL.random_model(rng, int(rng.integers(1, 20))) if i % 3 == 0 else profile(int(rng.integers(0, 12)))
+        if i % 50 == 7:
+            m = WL.Model(m.h, m.alpha, -m.beta, m.rho)
+        w = min(left, int(rng.integers(1, 400)))
+        lambdas.append(np.sort(np.exp(rng.uniform(np.log(0.5), np.log(200.0), size=w))))
+        if i % 20 == 3:
+            lambdas[-1][w // 2] = np.inf
+        models.append(m)
+        left -= w
+    c = WL.uniform_grid(120.0, 0.7, 1100)
+    got = dev_batch(torch_dev, ctx, c, models, lambdas, prec, flags)
+    assert len(got[1]) == n
+    h = len(models) // 2
+    parts = [dev_batch(torch_dev, ctx, c, models[s], lambdas[s], prec, flags) for s in (slice(0, h), slice(h, None))]
+    for x, *y, what in zip(got, *parts, ("C_t", "idx", "status", "c_ref")):
+        np.testing.assert_array_equal(x, np.concatenate(y), err_msg=what)
+    if flags == 0:
+        compare("staged picks", [g[:20] for g in got], *oracle_curve(lambdas[0][:20], c, models[0]), lambdas[0][:20],
+                c, models[0])
