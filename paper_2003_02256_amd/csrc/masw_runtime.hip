@@ -417,9 +417,9 @@ int run_curves(masw_ctx* ctx, const Inputs& in, masw_precision prec, uint32_t fl
   // wavelengths x 9,501 velocities 1.48 and 1.49 (split 1.09 and 1.09), 36,281
   // 2.78 and 2.67 (1.60 and 1.34), 69,443 5.43 and 5.20 (3.10 and 2.43); x
   // 19,001 velocities 36,469 5.14 and 5.23 (2.66 and 2.33), 70,340 10.70 and
-  // 10.67 (5.55 and 4.92).
-  const bool staged = !inertia && !in.misfit && G == 1 && ci.n_coop == 0 &&
-                      int64_t(in.n_lam) > 48 * 4 * int64_t(ctx->cus);
+  // 10.67 (5.55 and 4.92).  Misfits are then a launch of their own as well.
+  const bool staged = !inertia && G == 1 && ci.n_coop == 0 &&
+                      int64_t(in.n_lam) > (mode == 1 ? 32 : 48) * 4 * int64_t(ctx->cus);
 
   // timed (a slot of the stamp ring) unless no-alloc or without a sweep
   masw_ctx::TimingSlot* T = nullptr;
@@ -462,7 +462,7 @@ int run_curves(masw_ctx* ctx, const Inputs& in, masw_precision prec, uint32_t fl
   sw.refine = (flags & MASW_NO_REFINE) ? 0 : 1;
   sw.refine_rel = ctx->refine_rel;
   sw.counters = p.counters;
-  if (in.misfit && !inertia) {  // the inertia search takes a separate misfit launch below
+  if (in.misfit && !inertia && !staged) {  // (a separate misfit launch below)
     sw.c_e = c_e_dev;
     sw.misfit = misfit_dev;
     sw.model_left = p.model_left;
@@ -476,7 +476,7 @@ int run_curves(masw_ctx* ctx, const Inputs& in, masw_precision prec, uint32_t fl
              : staged ? launch_staged_picks(mode, ctx->cus, s, sw, &blocks)
                       : launch_sweep(mode, G, blocks, s, sw));
   if (T && T->events) MASW_HIP(hipEventRecord(T->ev[2], s));
-  if (in.misfit && inertia)
+  if (in.misfit && (inertia || staged))
     MASW_HIP(launch_misfit(in.n_models, p.lambda_off, sw.out_ct, c_e_dev, misfit_dev, s));
   // optional diagnostic after the timed sweep: the FP64 noise band of each
   // pick's bracket
