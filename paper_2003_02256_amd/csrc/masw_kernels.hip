@@ -1,7 +1,13 @@
 // HIP kernels for gfx950: staging/precompute, work ordering, the FP64 batch
 // sweep kernels (the sweep itself is in masw_sweep.hpp; the split kernels
-// are built in masw_sweep_split.hip), the serving tick, the misfit and the
-// full-grid sign map, and the host launchers.
+// are built in masw_sweep_split.hip), the serving tick and the misfit, and the
+// host launchers.
+//
+// The eliminations of K here (refinement, FP64 checks, the inertia search of
+// the ticks) materialise every polynomial coefficient in SGPRs where it is
+// used: with the series' in VGPRs the sweep kernels spilled (6000 wavelengths
+// of 3 layers in 208 us against 183), and nothing ran faster.
+#define MASW_COEFF_POLICY 1
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -607,48 +613,6 @@ hipError_t launch_misfit(int n_models, const int32_t* lambda_off, const double* 
   return hipGetLastError();
 }
 
-// ------------------------------------------------------------ sign map --
-// Every (wavelength, grid point) of model 0, no early exit: blockIdx.y is
-// the wavelength, x covers the grid.
-template <typename T>
-__global__ __launch_bounds__(256) void sign_map_kernel(SignMapArgs a) {
-  const int w = blockIdx.y;
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= a.n_c) return;
-  const ModelDesc d = a.models[0];
-  const double k64 = a.lam_k[w];
-  const size_t o = size_t(w) * size_t(a.n_c) + size_t(i);
-  if (!(k64 == k64)) {
-    a.sigma[o] = int8_t(kNaNSign);
-    if (a.logabs) a.logabs[o] = __builtin_nan("");
-    return;
-  }
-  const int N = uniform(d.n_layers);
-  const double c = a.c64[d.c_base + i];
-  int sg;
-  if constexpr (sizeof(T) == 8) {
-    const LayerRec64* L = a.layers64 + uniform(d.layer_base);
-    if (a.logabs) {
-      double la;
-      sg = det_sign_logabs<double>(c, k64, L, N, k64 * L[N].aux, &la);
-      a.logabs[o] = la;
-    } else {
-      sg = det_sign<double, false>(c, k64, L, N, nullptr);
-    }
-  } else {
-    const LayerRec32* L = a.layers32 + uniform(d.layer_base);
-    const LayerRec64* L64 = a.layers64 + uniform(d.layer_base);
-    if (a.logabs) {
-      double la;
-      sg = det_sign_logabs<float>(float(c), float(k64), L, N, k64 * L64[N].aux, &la);
-      a.logabs[o] = la;
-    } else {
-      sg = det_sign<float, false>(float(c), float(k64), L, N, nullptr);
-    }
-  }
-  a.sigma[o] = int8_t(sg);
-}
-
 // ------------------------------------------------------- no-alloc scratch --
 // Workspace of masw_dispersion_curve_noalloc: one static array per device
 // (each device that loads the library holds its own copy until the process
@@ -775,16 +739,6 @@ hipError_t launch_tick(int G, int blocks, hipStream_t s, const TickArgs& a) {
   if (!f) return hipErrorInvalidValue;
   void* args[] = {const_cast<TickArgs*>(&a)};
   return hipLaunchKernel(f, dim3(blocks), dim3(64 * G), args, 0, s);
-}
-
-hipError_t launch_sign_map(bool fp32, const SignMapArgs& a, hipStream_t s) {
-  if (a.n_lam == 0 || a.n_c == 0) return hipSuccess;
-  const dim3 grid((a.n_c + 255) / 256, a.n_lam);
-  if (fp32)
-    hipLaunchKernelGGL(sign_map_kernel<float>, grid, dim3(256), 0, s, a);
-  else
-    hipLaunchKernelGGL(sign_map_kernel<double>, grid, dim3(256), 0, s, a);
-  return hipGetLastError();
 }
 
 }  // namespace masw

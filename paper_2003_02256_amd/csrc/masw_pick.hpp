@@ -201,10 +201,7 @@ __device__ __forceinline__ unsigned long long refine_and_write(const ItemOut& o,
   const int lane = threadIdx.x & 63;
   unsigned long long evals = 0;
   int status = MASW_STATUS_FOUND;
-  if (sig_f == kNaNSign || prev_f == kNaNSign) {
-    if (confirm) return kUnconfirmed;
-    status = MASW_STATUS_NAN;
-  }
+  if (!confirm && (sig_f == kNaNSign || prev_f == kNaNSign)) status = MASW_STATUS_NAN;
   double c_ref = __builtin_nan("");
   if (status == MASW_STATUS_FOUND) {
     Refine8<true> r;

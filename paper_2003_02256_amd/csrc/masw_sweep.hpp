@@ -588,21 +588,26 @@ __device__ __forceinline__ bool run_item(const ItemRef& r, ItemState& st, int bu
   // next barrier.  One wavefront at a time on a SIMD finishes these few
   // rounds sooner than the whole group sharing the SIMDs would.
   if (wave == 0) {
-    bool confirm = fp64;  // (the split path's window has the determinant's own signs)
-    for (;;) {
-      const unsigned long long n = refine_and_write(o, r.c64, r.k64, r.L64, r.N, found, sig_f, prev_f, confirm);
+    // With a sweep's sign (the split path's window has the determinant's own)
+    // the determinant may change a step further up or down, the grid point
+    // between lying within rounding of the root (one pick in 10^7), or
+    // further away on a grid finer than that.
+    constexpr int kReach = 128;
+    int at = found;
+    for (int away = 1;; ++away) {
+      const unsigned long long n = refine_and_write(o, r.c64, r.k64, r.L64, r.N, at, sig_f, prev_f, fp64);
       wc.refine += n & ~kUnconfirmed;
       if (!(n & kUnconfirmed)) break;
-      // A sign within rounding of the change (one pick in 10^7) or no number:
-      // Algorithm 1 by the elimination, by this wavefront alone.
-      inertia::Tally t;
-      found = inertia::walk(r.c64, n_c, r.k64, r.L64, r.N, 0, kNoSign, &sig_f, &prev_f, t);
-      wc.sweep += t.scan;
-      if (found < 0) {
-        write_no_pick(o, MASW_STATUS_NOT_FOUND, lane == 0);
+      if (away > 2 * kReach) {  // no change of a number anywhere near
+        if (lane == 0) {
+          *o.idx = found;
+          *o.status = MASW_STATUS_NAN;
+          *o.ct = r.c64[found];
+          if (o.cref) *o.cref = __builtin_nan("");
+        }
         break;
       }
-      confirm = false;
+      at = max(1, min(n_c - 1, found + ((away & 1) ? (away + 1) / 2 : -(away / 2))));
     }
   }
   return true;
