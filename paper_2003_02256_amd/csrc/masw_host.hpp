@@ -30,7 +30,8 @@ hipError_t launch_sweep(int mode, int G, int blocks, hipStream_t s, const SweepA
 // wavefronts, one wavelength each.
 hipError_t launch_fused(int mode, int blocks, hipStream_t s, const SweepArgs& a);
 // The same with one wavefront per item, in three launches (masw_picks.hip).
-hipError_t launch_staged_picks(int mode, int cus, hipStream_t s, const SweepArgs& a, int* blocks_out);
+// *rows: the rows of a.wg_counts they write.
+hipError_t launch_staged_picks(int mode, int cus, hipStream_t s, const SweepArgs& a, int* blocks_out, int* rows);
 // The inertia-count search (masw_inertia.hip), one wavefront per wavelength.
 hipError_t launch_inertia(const SweepArgs& a, int cus, hipStream_t s, int* blocks_out);
 hipError_t launch_prep(const PrepArgs& a, const CoopInitArgs& ci, int single_N, int single_W, hipStream_t s);

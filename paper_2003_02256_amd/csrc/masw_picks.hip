@@ -191,10 +191,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void p
     }
   }
   wc.useful = inertia::wave_sum(wc.useful);
-  if ((threadIdx.x & 63) == 0) {
-    if (wc.check) atomicAdd(&a.counters->check, wc.check);
-    atomicAdd(&a.counters->refine, wc.refine);
-    atomicAdd(&a.counters->useful, wc.useful);
+  if ((threadIdx.x & 63) == 0) {  // a row of counts for each wavefront
+    unsigned long long* row = a.wg_counts + (size_t(blockIdx.x) * 4 + (threadIdx.x >> 6)) * kWgCounts;
+    row[0] = row[4] = row[5] = row[6] = row[7] = 0ull;
+    row[1] = wc.check;
+    row[2] = wc.refine;
+    row[3] = wc.useful;
   }
   stamp_end(a.tstamp);
 }
@@ -203,9 +205,8 @@ template <int MODE>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void pick_rest_kernel(SweepArgs a) {
   __shared__ SweepShared<1> sh;
   const unsigned n = a.counters->deferred;
-  if (n == 0u) return;
   WorkCount wc;
-  for (;;) {
+  while (n != 0u) {
     unsigned i = 0;
     if (threadIdx.x == 0) i = atomicAdd(&a.counters->rest_head, 1u);
     i = unsigned(uniform(int(i)));
@@ -216,28 +217,35 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void pi
     ItemState st = item_state_init();
     run_item<MODE, 1, true>(r, st, 0x7fffffff, sh, wc, o, kNoCoop, a.counters, uniform(*o.status));
   }
-  if (wc.refine + wc.check + wc.sweep != 0ull) flush_counts(a.counters, nullptr, wc);
-  stamp_end(a.tstamp);
+  flush_counts(a.counters, a.wg_counts, wc);
+  if (n != 0u) stamp_end(a.tstamp);
 }
 
+// Each launch's rows of work counts follow those of the one before; *rows is
+// their number (at most cus (28 + 16 + 16), below the smallest item count).
 template <int MODE>
-hipError_t launch(int cus, hipStream_t s, const SweepArgs& a, int* blocks_out) {
+hipError_t launch(int cus, hipStream_t s, const SweepArgs& a, int* blocks_out, int* rows) {
   // wavelengths a wavefront takes at a time: as launch_inertia's runs
   const int chunk = int(std::max<int64_t>(8, std::min<int64_t>(64, int64_t(a.n_items) / (int64_t(cus) * 32) / 8 * 8)));
   const int64_t runs = (int64_t(a.n_items) + chunk - 1) / chunk;
-  const int64_t blocks = std::min<int64_t>(a.n_items, int64_t(cus) * 4 * kSweepWaves<MODE>);
-  *blocks_out = int(blocks);
-  hipLaunchKernelGGL(first_change_kernel<MODE>, dim3(unsigned(blocks)), dim3(64), 0, s, a);
-  hipLaunchKernelGGL(pick_kernel<MODE>, dim3(unsigned(std::min<int64_t>((runs + 3) / 4, int64_t(cus) * 4))), dim3(256),
-                     0, s, a, chunk);
-  hipLaunchKernelGGL(pick_rest_kernel<MODE>, dim3(unsigned(cus) * 16), dim3(64), 0, s, a);
+  const int blocks = int(std::min<int64_t>(a.n_items, int64_t(cus) * 4 * kSweepWaves<MODE>));
+  const int picking = int(std::min<int64_t>((runs + 3) / 4, int64_t(cus) * 4)), rest = cus * 16;
+  *blocks_out = blocks;
+  *rows = blocks + 4 * picking + rest;
+  SweepArgs b = a;
+  hipLaunchKernelGGL(first_change_kernel<MODE>, dim3(blocks), dim3(64), 0, s, b);
+  b.wg_counts += size_t(blocks) * kWgCounts;
+  hipLaunchKernelGGL(pick_kernel<MODE>, dim3(picking), dim3(256), 0, s, b, chunk);
+  b.wg_counts += size_t(picking) * 4 * kWgCounts;
+  hipLaunchKernelGGL(pick_rest_kernel<MODE>, dim3(rest), dim3(64), 0, s, b);
   return hipGetLastError();
 }
 
 }  // namespace
 
-hipError_t launch_staged_picks(int mode, int cus, hipStream_t s, const SweepArgs& a, int* blocks_out) {
-  return mode == kModeFP64 ? launch<kModeFP64>(cus, s, a, blocks_out) : launch<kModeSplit>(cus, s, a, blocks_out);
+hipError_t launch_staged_picks(int mode, int cus, hipStream_t s, const SweepArgs& a, int* blocks_out, int* rows) {
+  return mode == kModeFP64 ? launch<kModeFP64>(cus, s, a, blocks_out, rows)
+                           : launch<kModeSplit>(cus, s, a, blocks_out, rows);
 }
 
 }  // namespace masw

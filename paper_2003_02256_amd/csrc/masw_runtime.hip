@@ -468,12 +468,13 @@ int run_curves(masw_ctx* ctx, const Inputs& in, masw_precision prec, uint32_t fl
     sw.model_left = p.model_left;
     sw.lambda_off = p.lambda_off;
   }
+  int count_rows = 0;  // (0: one per workgroup)
   if (T && T->events && !fused) MASW_HIP(hipEventRecord(T->ev[1], s));
   if (fused)
     MASW_HIP(launch_fused(mode, blocks, s, sw));
   else if (in.n_lam > 0)
     MASW_HIP(inertia  ? launch_inertia(sw, ctx->cus, s, &blocks)
-             : staged ? launch_staged_picks(mode, ctx->cus, s, sw, &blocks)
+             : staged ? launch_staged_picks(mode, ctx->cus, s, sw, &blocks, &count_rows)
                       : launch_sweep(mode, G, blocks, s, sw));
   if (T && T->events) MASW_HIP(hipEventRecord(T->ev[2], s));
   if (in.misfit && (inertia || staged))
@@ -494,7 +495,7 @@ int run_curves(masw_ctx* ctx, const Inputs& in, masw_precision prec, uint32_t fl
   ctx->last.split_as_fp64 = split_as_fp64 ? 1 : 0;
   ctx->last.workgroups = in.n_lam > 0 ? blocks : 0;
   ctx->wg_counts = sw.wg_counts;
-  ctx->wg_rows = in.n_lam > 0 ? blocks : 0;
+  ctx->wg_rows = in.n_lam <= 0 ? 0 : count_rows ? count_rows : blocks;
   ctx->last.shared_items = ci.n_coop;
   ctx->stats_pending = true;
   ctx->cls_pending = false;
