@@ -789,7 +789,7 @@ __device__ void model_finished(const SweepArgs& a, int m, SweepShared<G>& sh, do
 // sweeps that workgroups with an empty queue join.  MISFIT: Algorithm 2 fused
 // (model_finished), an instantiation of its own so that the plain sweeps
 // keep their register allocation; it and the plain FP64 sweeps are held to
-// 128 VGPRs (4 wavefronts per SIMD), spilling a little outside the layer loop.
+// 128 VGPRs (4 wavefronts per SIMD), which they fit without spilling.
 // The plain split sweeps are held to 96 VGPRs (5 wavefronts per SIMD), which
 // their FP32 loop fits without spilling.
 template <int MODE, int G, bool MISFIT>
