@@ -32,7 +32,7 @@ hipError_t launch_fused(int mode, int blocks, hipStream_t s, const SweepArgs& a)
 // The same with one wavefront per item, in three launches (masw_picks.hip).
 // *rows: the rows of a.wg_counts they write.
 hipError_t launch_staged_picks(int mode, int cus, hipStream_t s, const SweepArgs& a, int* blocks_out, int* rows);
-// The inertia-count search (masw_inertia.hip), one wavefront per wavelength.
+// The inertia-count search (masw_inertia.hip), 64, 32 or 8 lanes per wavelength.
 hipError_t launch_inertia(const SweepArgs& a, int cus, hipStream_t s, int* blocks_out);
 hipError_t launch_prep(const PrepArgs& a, const CoopInitArgs& ci, int single_N, int single_W, hipStream_t s);
 hipError_t launch_sign_map(bool fp32, const SignMapArgs& a, hipStream_t s);
@@ -105,6 +105,12 @@ struct masw_ctx {
   int wg_rows = 0;
   bool last_fused = false;  // the last timed launch staged inside the sweep (SweepArgs::fused)
   bool fused_small = true;  // small single-curve launches fuse the staging (MASW_FUSED_SMALL=0: never)
+  // Pinned block through which small host-pointer calls pass their inputs
+  // (front half) and outputs (back half) in one copy each way.  Used with mu
+  // held, and by calls that end with their stream synchronised.  Null if it
+  // could not be allocated: every array is then copied by itself.
+  static constexpr size_t kPinHalf = size_t(256) << 10;
+  char* pin = nullptr;
   char* arena = nullptr;
   size_t arena_size = 0;          // whole HBM budget
   size_t sync_size = 0;           // front part used by the synchronous calls

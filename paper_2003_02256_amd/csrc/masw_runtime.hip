@@ -278,7 +278,6 @@ int run_curves(masw_ctx* ctx, const Inputs& in, masw_precision prec, uint32_t fl
   p.models = b.take<ModelDesc>(size_t(in.n_models));
   p.layers64 = b.take<LayerRec64>(R);
   p.layers32 = b.take<LayerRec32>(R);
-  double* c_copy = dev ? nullptr : b.take<double>(size_t(in.n_c));
   p.c32 = b.take<float>(size_t(in.n_c));
   p.lam_k = b.take<double>(size_t(in.n_lam));
   p.lam_model = b.take<int32_t>(size_t(in.n_lam));
@@ -304,31 +303,38 @@ int run_curves(masw_ctx* ctx, const Inputs& in, masw_precision prec, uint32_t fl
     sw.out_status = out->status;
     sw.out_cref = out->c_ref;
   } else {
-    int32_t* loff = nullptr;
-    int32_t* woff = nullptr;
-    if (in.layer_off) {
-      loff = b.take<int32_t>(size_t(in.n_models) + 1);
-      woff = b.take<int32_t>(size_t(in.n_models) + 1);
-    } else {
-      b.take<int32_t>(size_t(in.n_models) + 1);
-      b.take<int32_t>(size_t(in.n_models) + 1);
-    }
+    int32_t* loff = b.take<int32_t>(size_t(in.n_models) + 1);
+    int32_t* woff = b.take<int32_t>(size_t(in.n_models) + 1);
+    char* const block = reinterpret_cast<char*>(loff);  // all inputs, through the pinned block if they fit
     double* hh = b.take<double>(size_t(in.n_layers_total));
     double* abr = b.take<double>(R * 3);
     double* ll = b.take<double>(size_t(in.n_lam));
-    if (loff) {
-      MASW_HIP(hipMemcpyAsync(loff, in.layer_off, sizeof(int32_t) * (in.n_models + 1), hipMemcpyHostToDevice, s));
-      MASW_HIP(hipMemcpyAsync(woff, in.lambda_off, sizeof(int32_t) * (in.n_models + 1), hipMemcpyHostToDevice, s));
+    double* c_copy = b.take<double>(size_t(in.n_c));
+    if (!b.ok()) return fail(MASW_ENOMEM, "workspace exceeds the HBM budget");
+    // A small pageable copy costs the host about 10 us whatever its size: six
+    // of them and four of outputs made most of the 151 us of a curve of 40
+    // wavelengths, which takes 58 us with one pinned copy each way.
+    const size_t block_bytes = size_t(reinterpret_cast<char*>(c_copy + in.n_c) - block);
+    const bool pinned = ctx->pin && block_bytes <= masw_ctx::kPinHalf;
+    auto put = [&](void* dst, const void* src, size_t bytes) -> hipError_t {
+      if (bytes == 0) return hipSuccess;
+      if (!pinned) return hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, s);
+      std::memcpy(ctx->pin + (static_cast<char*>(dst) - block), src, bytes);
+      return hipSuccess;
+    };
+    if (in.layer_off) {
+      MASW_HIP(put(loff, in.layer_off, sizeof(int32_t) * (in.n_models + 1)));
+      MASW_HIP(put(woff, in.lambda_off, sizeof(int32_t) * (in.n_models + 1)));
     }
-    if (in.n_layers_total)
-      MASW_HIP(hipMemcpyAsync(hh, in.h, sizeof(double) * in.n_layers_total, hipMemcpyHostToDevice, s));
-    MASW_HIP(hipMemcpyAsync(abr, in.alpha, sizeof(double) * R, hipMemcpyHostToDevice, s));
-    MASW_HIP(hipMemcpyAsync(abr + R, in.beta, sizeof(double) * R, hipMemcpyHostToDevice, s));
-    MASW_HIP(hipMemcpyAsync(abr + 2 * R, in.rho, sizeof(double) * R, hipMemcpyHostToDevice, s));
-    if (in.n_lam) MASW_HIP(hipMemcpyAsync(ll, in.lambda, sizeof(double) * in.n_lam, hipMemcpyHostToDevice, s));
-    MASW_HIP(hipMemcpyAsync(c_copy, in.c, sizeof(double) * in.n_c, hipMemcpyHostToDevice, s));
-    p.layer_off = loff;
-    p.lambda_off = woff;
+    MASW_HIP(put(hh, in.h, sizeof(double) * in.n_layers_total));
+    MASW_HIP(put(abr, in.alpha, sizeof(double) * R));
+    MASW_HIP(put(abr + R, in.beta, sizeof(double) * R));
+    MASW_HIP(put(abr + 2 * R, in.rho, sizeof(double) * R));
+    MASW_HIP(put(ll, in.lambda, sizeof(double) * in.n_lam));
+    MASW_HIP(put(c_copy, in.c, sizeof(double) * in.n_c));
+    if (pinned) MASW_HIP(hipMemcpyAsync(block, ctx->pin, block_bytes, hipMemcpyHostToDevice, s));
+    p.layer_off = in.layer_off ? loff : nullptr;
+    p.lambda_off = in.layer_off ? woff : nullptr;
     p.h = hh;
     p.alpha = abr;
     p.beta = abr + R;
@@ -504,7 +510,12 @@ int run_curves(masw_ctx* ctx, const Inputs& in, masw_precision prec, uint32_t fl
 
   if (!dev) {
     const size_t W = size_t(in.n_lam);
-    if (W) {
+    // the outputs lie one after the other in the workspace, c_t first
+    const size_t out_bytes = size_t(reinterpret_cast<char*>(sw.out_status + W) - reinterpret_cast<char*>(sw.out_ct));
+    const bool pinned = W && ctx->pin && out_bytes <= masw_ctx::kPinHalf;
+    if (pinned) {
+      MASW_HIP(hipMemcpyAsync(ctx->pin + masw_ctx::kPinHalf, sw.out_ct, out_bytes, hipMemcpyDeviceToHost, s));
+    } else if (W) {
       MASW_HIP(hipMemcpyAsync(out->c_t, sw.out_ct, sizeof(double) * W, hipMemcpyDeviceToHost, s));
       MASW_HIP(hipMemcpyAsync(out->idx, sw.out_idx, sizeof(int32_t) * W, hipMemcpyDeviceToHost, s));
       MASW_HIP(hipMemcpyAsync(out->status, sw.out_status, sizeof(int32_t) * W, hipMemcpyDeviceToHost, s));
@@ -514,6 +525,16 @@ int run_curves(masw_ctx* ctx, const Inputs& in, masw_precision prec, uint32_t fl
     if (in.misfit)
       MASW_HIP(hipMemcpyAsync(in.misfit, misfit_dev, sizeof(double) * in.n_models, hipMemcpyDeviceToHost, s));
     MASW_HIP(hipStreamSynchronize(s));
+    if (pinned) {
+      auto get = [&](void* dst, const void* src, size_t bytes) {
+        std::memcpy(dst, ctx->pin + masw_ctx::kPinHalf + (static_cast<const char*>(src) - reinterpret_cast<char*>(sw.out_ct)),
+                    bytes);
+      };
+      get(out->c_t, sw.out_ct, sizeof(double) * W);
+      get(out->idx, sw.out_idx, sizeof(int32_t) * W);
+      get(out->status, sw.out_status, sizeof(int32_t) * W);
+      if (out->c_ref) get(out->c_ref, sw.out_cref, sizeof(double) * W);
+    }
   }
   return MASW_OK;
 }
@@ -562,6 +583,7 @@ int masw_create(int device, size_t hbm_budget_bytes, masw_ctx** out) {
   auto cleanup = [&](int code, const std::string& msg) {
     if (ctx->arena) (void)hipFree(ctx->arena);
     if (ctx->tring) (void)hipFree(ctx->tring);
+    if (ctx->pin) (void)hipHostFree(ctx->pin);
     for (auto& e : ctx->cls_ev)
       if (e) (void)hipEventDestroy(e);
     delete ctx;
@@ -584,6 +606,10 @@ int masw_create(int device, size_t hbm_budget_bytes, masw_ctx** out) {
   for (auto& e : ctx->cls_ev)
     if (hipEventCreateWithFlags(&e, hipEventReleaseToDevice) != hipSuccess)
       return cleanup(MASW_EDEVICE, "hipEventCreate failed");
+  if (hipHostMalloc(reinterpret_cast<void**>(&ctx->pin), 2 * masw_ctx::kPinHalf, hipHostMallocDefault) != hipSuccess) {
+    ctx->pin = nullptr;
+    (void)hipGetLastError();
+  }
   if (hipMalloc(&ctx->arena, budget) != hipSuccess) return cleanup(MASW_ENOMEM, "cannot allocate the HBM budget");
   ctx->arena_size = budget;
   ctx->sync_size = budget;
@@ -623,6 +649,7 @@ void masw_destroy(masw_ctx* ctx) {
   if (ctx->last_valid) (void)hipStreamSynchronize(ctx->last_stream);
   if (ctx->arena) (void)hipFree(ctx->arena);
   if (ctx->tring) (void)hipFree(ctx->tring);
+  if (ctx->pin) (void)hipHostFree(ctx->pin);
   for (auto& t : ctx->tslot)
     for (auto& e : t.ev)
       if (e) (void)hipEventDestroy(e);
