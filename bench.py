@@ -55,6 +55,15 @@ def flops_per_eval(n_layers: float) -> float:
     return 101.0 * n_layers + 48.0
 
 
+def sweep_flops(evals: int, others: int, n_layers: float) -> float:
+    """Algorithmic FP operations of a sweep launch by the same rules: `evals`
+    signs from the dispersion function in minors, 66 per layer (4 for r^2 and
+    s^2, 2 for k h, 1 for the energy bound, 10 for each potential, 25 to turn
+    the minors, 14 for the interface) plus 20 for the surface and the
+    half-space, and `others` eliminations (re-check and refinement)."""
+    return evals * (66.0 * n_layers + 20.0) + others * flops_per_eval(n_layers)
+
+
 def inertia_flops(evals: int, entries: int, pivots: int) -> float:
     """Algorithmic FP operations of the inertia counts of a launch, from its
     work counters (the rules of flops_per_eval): 67 per element matrix formed
@@ -664,19 +673,27 @@ def measure_curves(M, torch, wl, steps: int, warmup: int, inertia: bool = True) 
     root_rel = np.abs(r32[3][both] - r64[3][both]) / r64[3][both]
 
     # algorithmic flops of one FP64 launch: the evaluations the method needs
-    # (every grid point up to each pick, plus the refinement) x F(N); rounds
+    # (every grid point up to each pick, plus the refinement); rounds
     # evaluated past a pick, speculatively or to fill a round, are not counted
     n_lay = np.asarray(job.n_layers)[job.lam_model]
     nbar = float(np.average(n_lay, weights=np.where(idx64 >= 0, idx64 + 1, wl.c_test.shape[0])))
     performed64 = st64["sweep_evals"] + st64["check_evals"] + st64["refine_evals"]
     algorithmic64 = st64["useful_evals"] + st64["check_evals"] + st64["refine_evals"]
-    flops64 = algorithmic64 * flops_per_eval(nbar)
+    flops64 = sweep_flops(st64["useful_evals"], st64["check_evals"] + st64["refine_evals"], nbar)
     achieved = flops64 / (sweep64 * 1e-3) / 1e12
-    algorithmic32 = st32["useful_evals"] + st32["check_evals"] + st32["refine_evals"]
-    achieved32 = algorithmic32 * flops_per_eval(nbar) / (sweep32 * 1e-3) / 1e12
+    achieved32 = (sweep_flops(st32["useful_evals"], st32["check_evals"] + st32["refine_evals"], nbar)
+                  / (sweep32 * 1e-3) / 1e12)
     n_curves = len(wl.models)
-    kname = ("fused_sweep_kernel<FP64>" if st64.get("fused_staging")
-             else f"sweep_kernel<FP64,G={st64['waves_per_item']}>")
+    def sweep_name(st, mode: str) -> str:
+        if st.get("fused_staging"):
+            return f"fused_sweep_kernel<{mode}>"
+        simds = 4 * torch.cuda.get_device_properties(0).multi_processor_count
+        if (st["waves_per_item"] == 1 and not st["shared_items"]
+                and st["n_lambda"] > (32 if mode == "split" else 48) * simds):
+            return f"first_change_kernel<{mode}>, pick_kernel, pick_rest_kernel"
+        return f"sweep_kernel<{mode},G={st['waves_per_item']}>"
+
+    kname = sweep_name(st64, "FP64")
     traffic = MEASURED_TRAFFIC.get((kernel_source_hash(), wl.name, kname))
     res = {
         "value": useful / wall64, "unit": "det evals/s", "ms_per_step": wall64 * 1e3, "dtype": "f64",
@@ -700,10 +717,7 @@ def measure_curves(M, torch, wl, steps: int, warmup: int, inertia: bool = True) 
             "curves_per_s": n_curves / wall32, "wavelengths_per_s": wl.n_lambda_total / wall32,
             "sweep_evals": st32["sweep_evals"], "check_evals": st32["check_evals"],
             "refine_evals": st32["refine_evals"], "sweep_kernel_ms": sweep32,
-            "kernel": (("fused_sweep_kernel<FP64>" if st32.get("fused_staging")
-                        else f"sweep_kernel<FP64,G={st32['waves_per_item']}>") if st32.get("split_as_fp64")
-                       else "fused_sweep_kernel<split>" if st32.get("fused_staging")
-                       else f"sweep_kernel<split,G={st32['waves_per_item']}>"),
+            "kernel": sweep_name(st32, "FP64" if st32.get("split_as_fp64") else "split"),
             "split_as_fp64": bool(st32.get("split_as_fp64")),
             "achieved_tflops_fp64_counted": achieved32,
             "idx_mismatch_vs_fp64": int(np.sum((idx64 != idx32))),
