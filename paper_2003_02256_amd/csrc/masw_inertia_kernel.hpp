@@ -243,9 +243,19 @@ __device__ __forceinline__ void run_groups(const SweepArgs& a, int begin, int en
       if (f == 0) end_as = 2;  // E(c_test[0]) is not 0
       if (f < S) hi = p_f;
       lo = p_b;
-      const bool can_try = f < S && last >= 3 && p_f - p_b <= kTrySpacing;
-      const double x = root_estimate<U>(double(p), v.m, v.e, base + max(0, min(f - 2, last - 3)),
-                                        base + min(max(f - 1, 0), S - 2));
+      bool can_try = f < S && last >= 3 && p_f - p_b <= kTrySpacing;
+      // Lone wavefronts, whose time is their rounds': where the points are
+      // further apart than 1% of c the cubic often misses the step, and one
+      // more Narrow round names it for certain (60 wavelengths x 1901
+      // velocities over 25 layers: 86.9 us without this, 74.2 with it).
+      if (S >= 32) {
+        const double c_f = from_lane<U>(c, base + min(f, S - 1)), c_b = from_lane<U>(c, base + max(b, 0));
+        can_try = can_try && c_f - c_b <= 0.01 * c_f;
+      }
+      double x = 0.0;
+      if (__ballot(can_try) != 0ull)
+        x = root_estimate<U>(double(p), v.m, v.e, base + max(0, min(f - 2, last - 3)),
+                             base + min(max(f - 1, 0), S - 2));
       stage = kNarrow;
       if (hi - lo == 1) {
         if (hi == n_c) end_as = end_as ? end_as : 1;                   // E = 0 at the last grid point
