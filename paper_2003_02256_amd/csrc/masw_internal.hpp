@@ -35,7 +35,8 @@ struct alignas(8 * sizeof(T)) LayerRec {
           // nothing reads, the depth of the layer's bottom (m) for the work-order key
   T h;    // thickness (0 for the half-space record)
   T aux;  // layer j: rho_j / rho_{j+1}; half-space record: mu_ref (Pa)
-  T idr;  // layer j: rho_{j+1} / rho_j; half-space record: 0
+  T idr;  // layer j: rho_{j+1} / rho_j; half-space record (FP64): the velocity from which on the
+          // sweep takes its sign in minors (masw_secular.hpp)
   T kap;  // layer j: 2 (mu_{j+1} - mu_j) / rho_{j+1}; half-space record: 0 (masw_secular.hpp)
 };
 using LayerRec64 = LayerRec<double>;
@@ -223,10 +224,11 @@ struct ItemState {
   int32_t seg_carry;  // split path: FP64 sign at seg_start - 1 (kNoSign at the grid start)
   int32_t done;       // 1 once the outputs are written
   int32_t fp64;       // split path: 1 once it fell back to the FP64 sweep
-  int32_t pad[2];
+  int32_t by_k;       // 1 once the FP64 sweep was begun again by the elimination alone
+  int32_t pad;
 };
 
-__host__ __device__ inline ItemState item_state_init() { return ItemState{0, kNoSign, 0, kNoSign, 0, 0, {0, 0}}; }
+__host__ __device__ inline ItemState item_state_init() { return ItemState{0, kNoSign, 0, kNoSign, 0, 0, 0, 0}; }
 
 // ------------------------------------------------------------- serving --
 constexpr int kMaxSlots = 256;     // requests resident on the device at once

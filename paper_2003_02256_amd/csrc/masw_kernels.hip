@@ -97,6 +97,7 @@ __device__ void build_model(const PrepArgs& a, int m, int single_N, int single_W
   if (!ok) return;
   const double mu_ref = a.rho[rec0 + N] * a.beta[rec0 + N] * a.beta[rec0 + N];
   double z0 = 0.0;  // depth of the top of this 64-layer chunk
+  double b_max = 0.0;
   for (int j0 = 0; j0 <= N; j0 += 64) {
     const int j = j0 + lane;
     // depth of each layer's bottom: inclusive prefix sum over the chunk
@@ -107,6 +108,9 @@ __device__ void build_model(const PrepArgs& a, int m, int single_N, int single_W
     }
     z += z0;
     z0 = __shfl(z, 63, 64);
+    b_max = __builtin_fmax(b_max, j <= N ? a.beta[rec0 + j] : 0.0);
+    if (j0 + 64 > N)
+      for (int off = 1; off < 64; off <<= 1) b_max = __builtin_fmax(b_max, __shfl_xor(b_max, off, 64));
     if (j > N) continue;
     const double al = a.alpha[rec0 + j], be = a.beta[rec0 + j], rh = a.rho[rec0 + j];
     LayerRec64 r;
@@ -118,7 +122,7 @@ __device__ void build_model(const PrepArgs& a, int m, int single_N, int single_W
     secular::Interface f{mu_ref, 0.0, 0.0};
     if (j < N) f = secular::interface_of(rh, be, a.rho[rec0 + j + 1], a.beta[rec0 + j + 1]);
     r.aux = f.dr;
-    r.idr = f.idr;
+    r.idr = j < N ? f.idr : b_max * secular::kLowest;
     r.kap = f.kap;
     a.layers64[rec0 + j] = r;
     LayerRec32 q;
@@ -385,6 +389,9 @@ __global__ __launch_bounds__(kAdmitChunk) void admit_kernel(const AdmitList* __r
   const bool valid = __syncthreads_or(bad) == 0;
   const double mu_ref = valid ? rho[N] * beta[N] * beta[N] : 0.0;
   if (valid) {
+    double b_max = 0.0;  // for the thread that writes the half-space's record
+    if (threadIdx.x == unsigned(N) % blockDim.x)
+      for (int j = 0; j <= N; ++j) b_max = __builtin_fmax(b_max, beta[j]);
     for (int j = threadIdx.x; j <= N; j += blockDim.x) {
       const double al = alpha[j], be = beta[j], rh = rho[j];
       LayerRec64 r;
@@ -396,7 +403,7 @@ __global__ __launch_bounds__(kAdmitChunk) void admit_kernel(const AdmitList* __r
       secular::Interface f{mu_ref, 0.0, 0.0};
       if (j < N) f = secular::interface_of(rh, be, rho[j + 1], beta[j + 1]);
       r.aux = f.dr;
-      r.idr = f.idr;
+      r.idr = j < N ? f.idr : b_max * secular::kLowest;
       r.kap = f.kap;
       d.L64[j] = r;
       LayerRec32 q;
@@ -498,7 +505,7 @@ __device__ __forceinline__ bool inertia_tick_item(const ItemRef& r, ItemState& s
     st.carry = carry;
     st.fp64 = 1;
   }
-  return run_item<kModeFP64, G>(r, st, budget, sh, wc, o, kNoCoop, cnt);
+  return run_item<kModeFP64, G, kFromTick>(r, st, budget, sh, wc, o, kNoCoop, cnt);
 }
 
 // One serving tick: every unfinished item of every active request advances by
@@ -546,6 +553,7 @@ void tick_kernel(TickArgs a) {
     r.c32 = sd.c32;
     r.L64 = as_global(sd.L64);
     r.L32 = as_global(sd.L32);
+    r.c_low = minors_from(r.L64, r.N);
     const int og = sd.out_base + j;
     const ItemOut o{a.out_ct + og, a.out_idx + og, a.out_status + og, a.out_cref + og,
                     (a.refine && !(sd.flags & MASW_NO_REFINE)) ? 1 : 0, a.refine_rel};
@@ -555,11 +563,11 @@ void tick_kernel(TickArgs a) {
       st.done = 1;
       done = true;
     } else if (sd.prec == MASW_PREC_SPLIT) {
-      done = run_item<kModeSplit, G>(r, st, budget, sh, wc, o, kNoCoop, a.counters);
+      done = run_item<kModeSplit, G, kFromTick>(r, st, budget, sh, wc, o, kNoCoop, a.counters);
     } else if (INERTIA) {
       done = inertia_tick_item<G>(r, st, budget, sh, wc, o, a.counters);
     } else {
-      done = run_item<kModeFP64, G>(r, st, budget, sh, wc, o, kNoCoop, a.counters);
+      done = run_item<kModeFP64, G, kFromTick>(r, st, budget, sh, wc, o, kNoCoop, a.counters);
     }
     if (threadIdx.x == 0) {
       sd.state[j] = st;

@@ -17,10 +17,11 @@
 //       there is no earlier change (masw_inertia.hpp).  Then, and on the walk
 //       at once, the refinement by eight points a round (Refine8), whose
 //       first round has K's own signs at the pick's two grid points.
-//   pick_rest_kernel: the others (no change found in FP32, a candidate that
-//       the eight points do not settle, a pole in the step or several changes,
-//       a sign within rounding of the change), by a whole wavefront each, as
-//       the one-launch sweep does them from the candidate on.
+//   pick_rest_kernel: the others (no change found in FP32, a grid that starts
+//       below c_low, a candidate that the eight points do not settle, a pole in
+//       the step or several changes, a change that the elimination does not
+//       confirm), by a whole wavefront each, as the one-launch sweep does them
+//       from the candidate on.
 // Between the launches out_idx holds the candidate, or kDeferredIdx with the
 // candidate (-1: none) in out_status.  Indices, statuses and roots are those
 // of the one-launch sweep: the same eliminations at the same points decide.
@@ -59,11 +60,13 @@ void first_change_kernel(SweepArgs a) {
       const int n = MODE == kModeFP64 ? r.n_c : r.n_real;
       const float k32 = float(r.k64);
       int carry = kNoSign, found = -1, sig_f, prev_f;
-      for (int base = 0; base < n; base += 64) {
+      // (a grid that starts below c_low is left to the last launch)
+      const bool low = MODE == kModeFP64 && r.c64[0] < r.c_low;
+      for (int base = 0; base < n && !low; base += 64) {
         const int i = base + lane;
         int sg = kNoSign;
         if (i < n) {
-          if constexpr (MODE == kModeFP64) sg = sweep_sign64(r.c64[i], r.k64, r.L64, r.N);
+          if constexpr (MODE == kModeFP64) sg = sweep_minors64(r.c64[i], r.k64, r.L64, r.N);
           else sg = sweep_code32(r.c32[i], k32, r.L32, r.N);
         }
         const int f = round_first_change<1>(sg, carry, nullptr, &carry, &sig_f, &prev_f);
@@ -73,7 +76,7 @@ void first_change_kernel(SweepArgs a) {
           break;
         }
       }
-      if (MODE == kModeFP64 && found < 0) {
+      if (MODE == kModeFP64 && found < 0 && !low && carry != kNaNSign) {
         write_no_pick(o, MASW_STATUS_NOT_FOUND, lane == 0);
         wc.useful += (unsigned long long)n;
       } else if (lane == 0) {
@@ -215,7 +218,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void pi
     const ItemRef r = item_of(a, g);
     const ItemOut o = item_out(a, g);
     ItemState st = item_state_init();
-    run_item<MODE, 1, true>(r, st, 0x7fffffff, sh, wc, o, kNoCoop, a.counters, uniform(*o.status));
+    run_item<MODE, 1, kFromRest>(r, st, 0x7fffffff, sh, wc, o, kNoCoop, a.counters, uniform(*o.status));
   }
   flush_counts(a.counters, a.wg_counts, wc);
   if (n != 0u) stamp_end(a.tstamp);

@@ -30,10 +30,25 @@
 // with p and q as they were.  This order of the sums, with no difference of
 // two large products, keeps the sign right to about 1e-15 relative in c around
 // a root on the profiles of the workloads (the elimination: 1e-14), and to
-// 8e-11 in the worst of 150 random profiles of strong contrasts (4e-12).  The
-// elimination has the last word all the same: the refinement evaluates it at
-// the two grid points of a pick (refine_and_write), and the split path checks
-// its candidates with it.
+// 8e-11 in the worst of 150 random profiles of strong contrasts (4e-12).
+//
+// At low c UU cancels to the order of (c/beta)^4 and meets y^2, which grows as
+// (beta/c)^4: where some layer is much stiffer than c, the sign is rounding
+// noise at velocities where the elimination's is exact.  Wrong signs away from
+// a root, of 4000 random models (1 to 7 layers, beta 100 to 3500 m/s) and of
+// 1500 with any contrast (1 to 30 layers, alpha/beta to 30, layers of 2 mm to
+// 300 m): none at velocities above 1/287 of the largest beta, and three above
+// 1/100, the highest at 1/52 (the elimination: 1/1083 and 1/229).  So
+// velocities below kLowest times the largest beta are swept by the elimination
+// (c_low, in the half-space's record).  The elimination has the last word all
+// the same: the refinement evaluates it at the two grid points of a pick, and
+// where it does not confirm the change the walk is made again by it alone
+// (walk_by_k).  Either of the two measures alone loses picks: 1067 of 31,000
+// random items of the two kinds, on grids from 0.3 to 50 m/s, without the
+// first.  With both, 253 of 196,000 items of the second kind are walked again,
+// and 7 picks are one to four grid steps from the elimination's first change,
+// which is itself within its rounding of the root there.  The split path checks
+// its candidates with the elimination.
 // At the surface (free) z1 = 4, z2 = -2 (2 - g), z3 = (2 - g)^2, p = q = 0;
 // over the half-space, whose potentials decay as exp(-r zeta), exp(-s zeta),
 //     F = r s z1 - z3 + r p + s q,
@@ -78,6 +93,9 @@ template <typename T>
 constexpr T kSeriesEnd = T(4) * kUnit<T> * kUnit<T>;
 template <typename T>
 constexpr T kBound = T(-9.86) * kUnit<T> * kUnit<T>;  // the energy bound's (t q)^2, inside pi^2
+
+// The lowest velocity swept in minors, over the largest beta (file comment).
+constexpr double kLowest = 1.0 / 64.0;
 
 // Interface constants of layer j over layer j + 1 (or the half-space), as
 // they are kept in layer j's record.

@@ -102,10 +102,18 @@ __device__ __forceinline__ int round_first_change(int sg, int prev0, WaveSum* su
   return w * 64 + __builtin_amdgcn_readlane(edge ? 0 : change - 1, w);
 }
 
-// The determinant's sign code of a grid point in the FP64 sweep.
-__device__ __forceinline__ int sweep_sign64(double c, double k, const LayerRec64* L, int N) {
+// The determinant's sign code of a grid point in the FP64 sweep: in minors, or
+// by the elimination in a wavefront with a point below c_low, where the minors
+// leave rounding alone (masw_secular.hpp).
+__device__ __forceinline__ int sweep_minors64(double c, double k, const LayerRec64* L, int N) {
   int odd;
   return secular::sign<double>(c, k, L, N, &odd);
+}
+template <bool LOW = true>
+__device__ __forceinline__ int sweep_sign64(double c, double k, const LayerRec64* L, int N, double c_low) {
+  if (LOW && __builtin_expect(__ballot(c < c_low) != 0ull, 0))
+    return det_sign<double, false>(c, k, L, N, nullptr);
+  return sweep_minors64(c, k, L, N);
 }
 
 // Sweep code of a grid point in the FP32 sweep: the determinant's sign code,
@@ -144,6 +152,7 @@ struct ItemRef {
   int N, n_c;
   int n_real;  // leading grid points below the half-space's S velocity (the FP32 sweep's extent)
   double k64;
+  double c_low;  // velocities below it are swept by the elimination
   const double* c64;
   const float* c32;
   const LayerRec64* L64;
@@ -155,6 +164,12 @@ struct ItemRef {
 // FP32 grid point i: the staged copy, or (c32 null: a fused launch) the FP64
 // value rounded here, which is the value the staging stores.
 __device__ __forceinline__ float c32_at(const ItemRef& r, int i) { return r.c32 ? r.c32[i] : float(r.c64[i]); }
+
+// Velocities below it are swept by the elimination: kept in the half-space's
+// record.
+__device__ __forceinline__ double minors_from(const LayerRec64* L, int N) {
+  return secular::load_layer<double>(L, N).idr;
+}
 
 template <typename T>
 __device__ __forceinline__ int sweep_len(const ItemRef& r) {
@@ -233,7 +248,7 @@ __device__ __forceinline__ int eval_round(const ItemRef& r, int rd, SweepShared<
   int sg = kNoSign;
   if (i < sweep_len<T>(r)) {
     if constexpr (sizeof(T) == 8)
-      sg = sweep_sign64(r.c64[i], r.k64, r.L64, r.N);
+      sg = sweep_sign64(r.c64[i], r.k64, r.L64, r.N, r.c_low);
     else
       sg = sweep_code32(c32_at(r, i), float(r.k64), r.L32, r.N);
   }
@@ -247,7 +262,8 @@ __device__ __forceinline__ int eval_round(const ItemRef& r, int rd, SweepShared<
 // rounds.  Thread 0 claims rounds one ahead (the claim's latency overlaps the
 // round), applies each round's summary in grid order with the carried sign
 // of the previous round, and waits only when it has no round of its own left.
-// Returns the change's position, -1 if the grid has none, or kCoopStall.
+// Returns the change's position, -1 if the grid has none (*prev is then its last
+// sign), or kCoopStall.
 template <typename T, int G>
 __device__ int coop_sweep(const ItemRef& r, const CoopRef& co, SweepShared<G>& sh, WorkCount& wc,
                           Counters* cnt, int* sig, int* prev) {
@@ -335,7 +351,7 @@ __device__ int coop_sweep(const ItemRef& r, const CoopRef& co, SweepShared<G>& s
           ++resolved;
         }
       }
-      if (!done && resolved >= n_rounds) done = true;  // no change in the grid
+      if (!done && resolved >= n_rounds) fp = carry, done = true;  // no change in the grid
       if (!done && nclaim >= bound && resolved >= bound) {
         // bound < n_rounds means round `stop` holds a change, which the loop
         // above must have found; anything else is a broken invariant.
@@ -366,6 +382,54 @@ __device__ int coop_sweep(const ItemRef& r, const CoopRef& co, SweepShared<G>& s
   }
 }
 
+// Whether a fused launch's grid starts below c_low (from the records in LDS).
+__device__ __forceinline__ bool starts_low(const ItemRef& r) {
+  static_assert(kFusedMaxLayers <= 64, "lane j looks at the records j and j + 1");
+  const int j = min(int(threadIdx.x) & 63, r.N);
+  const double ib2 = __builtin_fmin(r.L64[j].ib2, r.L64[min(j + 1, r.N)].ib2);
+  const double c = r.c64[0] * (1.0 / secular::kLowest);
+  return __ballot(c * c * ib2 < 1.0) != 0ull;
+}
+
+// Algorithm 1's scan by the elimination alone, from st.start on, with the
+// refinement and outputs; returns as run_item does.  For an item whose sign in
+// minors the elimination did not confirm (a grid point within rounding of the
+// root, one pick in 10^7; or a model on which the minors are rounding noise
+// above c_low too), or whose minors are not a number throughout.
+template <int G>
+__device__ __forceinline__ bool walk_by_k(const ItemRef& r, ItemState& st, int budget, SweepShared<G>& sh,
+                                          WorkCount& wc, const ItemOut& o) {
+  constexpr int P = 64 * G;
+  const int n_c = r.n_c;
+  int found = -1, sig_f = 0, prev_f = 0, rounds = 0;
+  int carry = st.carry;
+  if constexpr (G > 1) __syncthreads();  // sh.sum of the sweep's last round has been read
+  for (int base = st.start; base < n_c; base += P) {
+    if (rounds == budget) {
+      st.start = base;
+      st.carry = carry;
+      return false;
+    }
+    ++rounds;
+    const int i = base + int(threadIdx.x);
+    const int sg = (i < n_c) ? det_sign<double, false>(r.c64[i], r.k64, r.L64, r.N, nullptr) : kNoSign;
+    const int f = round_first_change<G>(sg, carry, sh.sum[rounds & 1], &carry, &sig_f, &prev_f);
+    wc.sweep += (unsigned long long)min(P, n_c - base);
+    if (f >= 0) {
+      found = base + f;
+      break;
+    }
+  }
+  st.done = 1;
+  wc.useful += (unsigned long long)(found < 0 ? n_c : found + 1);
+  if (found < 0) {
+    write_missing<G>(o, MASW_STATUS_NOT_FOUND);
+  } else if ((threadIdx.x >> 6) == 0) {
+    wc.refine += refine_and_write(o, r.c64, r.k64, r.L64, r.N, found, sig_f, prev_f);
+  }
+  return true;
+}
+
 // Advance one item by at most `budget` sweep rounds of G*64 positions.  When
 // the first sign change is known (after the FP64 re-check for the split
 // path), refine it in FP64 and write the outputs through wavefront 0, then
@@ -390,11 +454,22 @@ __device__ int coop_sweep(const ItemRef& r, const CoopRef& co, SweepShared<G>& s
 // from the segment's origin; the grid above the half-space's S velocity is
 // walked in FP64.  So the split pick is Algorithm 1's pick in FP64 (up to
 // the noise band of the FP64 signs and counts).
-// SWEPT: the first sweep has been made, by another launch; its candidate is
-// `swept` (-1: none).
-template <int MODE, int G, bool SWEPT = false>
+// FROM: the kernel that runs the item.
+//   kFromSweep: a batch launch.
+//   kFromRest:  the first sweep has been made, by another launch; its candidate
+//               is `swept` (-1: none).
+//   kFromFused: the sweep in minors does not look at c_low, which would put a
+//               wait in front of its first round (0.35 us of the 11 us of 30
+//               wavelengths x 801 velocities); wavefront 1 does while the first
+//               one refines.
+//   kFromTick:  resumed in later ticks; a walk by the elimination begins in the
+//               next one.
+enum { kFromSweep, kFromRest, kFromFused, kFromTick };
+template <int MODE, int G, int FROM>
 __device__ __forceinline__ bool run_item(const ItemRef& r, ItemState& st, int budget, SweepShared<G>& sh, WorkCount& wc,
                          const ItemOut& o, const CoopRef& co, Counters* cnt, int swept = 0) {
+  constexpr bool SWEPT = FROM == kFromRest;
+  if (FROM == kFromTick && st.by_k) return walk_by_k<G>(r, st, budget, sh, wc, o);
   constexpr int P = 64 * G;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -550,7 +625,10 @@ __device__ __forceinline__ bool run_item(const ItemRef& r, ItemState& st, int bu
     }
   }
   if constexpr (SWEPT && MODE == kModeFP64) {
-    found = swept;
+    if (swept >= 0) {
+      found = swept;
+      fp64 = false;  // (walked)
+    }
   } else if (fp64 && MODE == kModeFP64 && co.ci) {
     found = coop_sweep<double, G>(r, co, sh, wc, cnt, &sig_f, &prev_f);
     if (found == kCoopStall) {
@@ -558,7 +636,10 @@ __device__ __forceinline__ bool run_item(const ItemRef& r, ItemState& st, int bu
       write_missing<G>(o, MASW_STATUS_INVALID);
       return true;
     }
-  } else if (fp64) {
+    carry = prev_f;
+    fp64 = false;
+  }
+  if (fp64) {
     for (int base = start; base < n_c; base += P) {
       if (rounds == budget) {
         st.start = base;
@@ -567,7 +648,7 @@ __device__ __forceinline__ bool run_item(const ItemRef& r, ItemState& st, int bu
       }
       ++rounds;
       const int i = base + tid;
-      const int sg = (i < n_c) ? sweep_sign64(r.c64[i], r.k64, r.L64, r.N) : kNoSign;
+      const int sg = (i < n_c) ? sweep_sign64<FROM != kFromFused>(r.c64[i], r.k64, r.L64, r.N, r.c_low) : kNoSign;
       const int f = round_first_change<G>(sg, carry, sh.sum[rounds & 1], &carry, &sig_f, &prev_f);
       wc.sweep += (unsigned long long)min(P, n_c - base);
       if (f >= 0) {
@@ -576,40 +657,39 @@ __device__ __forceinline__ bool run_item(const ItemRef& r, ItemState& st, int bu
       }
     }
   }
-  st.done = 1;
-
-  wc.useful += (unsigned long long)(found < 0 ? n_c : found + 1);
-  if (found < 0) {
-    write_missing<G>(o, MASW_STATUS_NOT_FOUND);
-    return true;
-  }
+  const bool minors = MODE == kModeFP64 || st.fp64;  // (the split path's window has the determinant's own sign)
 
   // Refinement and output by wavefront 0 alone; the others go on to the
   // next barrier.  One wavefront at a time on a SIMD finishes these few
   // rounds sooner than the whole group sharing the SIMDs would.
-  if (wave == 0) {
-    // With a sweep's sign (the split path's window has the determinant's own)
-    // the determinant may change a step further up or down, the grid point
-    // between lying within rounding of the root (one pick in 10^7), or
-    // further away on a grid finer than that.
-    constexpr int kReach = 128;
-    int at = found;
-    for (int away = 1;; ++away) {
-      const unsigned long long n = refine_and_write(o, r.c64, r.k64, r.L64, r.N, at, sig_f, prev_f, fp64);
+  // With a sign in minors the refinement confirms by the elimination that the
+  // determinant changes.
+  static_assert(FROM != kFromFused || G > 1, "wavefront 1 looks at c_low");
+  bool again = minors && found < 0 && (carry == kNaNSign || (FROM == kFromFused && starts_low(r)));
+  if (found >= 0) {
+    if (wave == 0) {
+      const unsigned long long n = refine_and_write(o, r.c64, r.k64, r.L64, r.N, found, sig_f, prev_f, minors);
       wc.refine += n & ~kUnconfirmed;
-      if (!(n & kUnconfirmed)) break;
-      if (away > 2 * kReach) {  // no change of a number anywhere near
-        if (lane == 0) {
-          *o.idx = found;
-          *o.status = MASW_STATUS_NAN;
-          *o.ct = r.c64[found];
-          if (o.cref) *o.cref = __builtin_nan("");
-        }
-        break;
-      }
-      at = max(1, min(n_c - 1, found + ((away & 1) ? (away + 1) / 2 : -(away / 2))));
+      again = (n & kUnconfirmed) != 0ull;
+      if (minors && lane == 0) sh.check[0] = again ? 1 : 0;
+    } else if (FROM == kFromFused && minors && wave == 1) {
+      const bool low = starts_low(r);
+      if (lane == 0) sh.check[1] = low ? 1 : 0;
+    }
+    if (minors && G > 1) {
+      __syncthreads();
+      again = (sh.check[0] | (FROM == kFromFused ? sh.check[1] : 0)) != 0;
     }
   }
+  if (__builtin_expect(again, 0)) {
+    st.by_k = 1;
+    st.start = 0;
+    st.carry = kNoSign;
+    return FROM == kFromTick ? false : walk_by_k<G>(r, st, 0x7fffffff, sh, wc, o);
+  }
+  st.done = 1;
+  wc.useful += (unsigned long long)(found < 0 ? n_c : found + 1);
+  if (found < 0) write_missing<G>(o, MASW_STATUS_NOT_FOUND);
   return true;
 }
 
@@ -648,6 +728,7 @@ __device__ __forceinline__ ItemRef item_of(const SweepArgs& a, int g, int* m_out
   r.c32 = a.c32 + uniform(d.c_base);
   r.L64 = a.layers64 + uniform(d.layer_base);
   r.L32 = a.layers32 + uniform(d.layer_base);
+  r.c_low = minors_from(r.L64, r.N);
   return r;
 }
 
@@ -839,7 +920,7 @@ void sweep_kernel(SweepArgs a) {
       co.active = a.coop_active + blockIdx.x;
     }
     ItemState st = item_state_init();
-    run_item<MODE, G>(r, st, 0x7fffffff, sh, wc, o, co, a.counters);
+    run_item<MODE, G, kFromSweep>(r, st, 0x7fffffff, sh, wc, o, co, a.counters);
     if constexpr (MISFIT) model_finished<G>(a, m, sh, s_mis);
   }
   __builtin_amdgcn_s_setprio(0);
@@ -940,7 +1021,7 @@ __global__ __launch_bounds__(64 * kFusedG) void fused_sweep_kernel(SweepArgs a) 
     write_missing<G>(o, MASW_STATUS_INVALID);
   } else {
     ItemState st = item_state_init();
-    run_item<MODE, G>(r, st, 0x7fffffff, sh, wc, o, kNoCoop, a.counters);
+    run_item<MODE, G, kFromFused>(r, st, 0x7fffffff, sh, wc, o, kNoCoop, a.counters);
   }
   flush_counts(a.counters, a.wg_counts, wc);
   stamp_end(a.tstamp);
