@@ -97,20 +97,19 @@ __device__ void build_model(const PrepArgs& a, int m, int single_N, int single_W
   if (!ok) return;
   const double mu_ref = a.rho[rec0 + N] * a.beta[rec0 + N] * a.beta[rec0 + N];
   double z0 = 0.0;  // depth of the top of this 64-layer chunk
-  double b_max = 0.0;
+  float b_max = 0.0f;  // the largest beta so far (in FP32: it only places a limit)
   for (int j0 = 0; j0 <= N; j0 += 64) {
     const int j = j0 + lane;
     // depth of each layer's bottom: inclusive prefix sum over the chunk
     double z = (j < N) ? a.h[lo + j] : 0.0;
+    b_max = __builtin_fmaxf(b_max, j <= N ? float(a.beta[rec0 + j]) : 0.0f);
     for (int off = 1; off < 64; off <<= 1) {
       const double up = __shfl_up(z, off, 64);
+      b_max = __builtin_fmaxf(b_max, __shfl_xor(b_max, off, 64));
       if (lane >= off) z += up;
     }
     z += z0;
     z0 = __shfl(z, 63, 64);
-    b_max = __builtin_fmax(b_max, j <= N ? a.beta[rec0 + j] : 0.0);
-    if (j0 + 64 > N)
-      for (int off = 1; off < 64; off <<= 1) b_max = __builtin_fmax(b_max, __shfl_xor(b_max, off, 64));
     if (j > N) continue;
     const double al = a.alpha[rec0 + j], be = a.beta[rec0 + j], rh = a.rho[rec0 + j];
     LayerRec64 r;
@@ -122,7 +121,7 @@ __device__ void build_model(const PrepArgs& a, int m, int single_N, int single_W
     secular::Interface f{mu_ref, 0.0, 0.0};
     if (j < N) f = secular::interface_of(rh, be, a.rho[rec0 + j + 1], a.beta[rec0 + j + 1]);
     r.aux = f.dr;
-    r.idr = j < N ? f.idr : b_max * secular::kLowest;
+    r.idr = j < N ? f.idr : double(b_max) * secular::kLowest;
     r.kap = f.kap;
     a.layers64[rec0 + j] = r;
     LayerRec32 q;
