@@ -85,6 +85,7 @@ hipError_t launch_inertia(const SweepArgs& a, int cus, hipStream_t s, int* block
     const int64_t runs = (int64_t(a.n_items) + chunk - 1) / chunk;
     const int64_t blocks = std::min<int64_t>((runs + kInertiaWaves - 1) / kInertiaWaves, int64_t(cus) * 4);
     *blocks_out = int(blocks);
+    if (blocks > a.wg_rows) return hipErrorInvalidValue;
     hipLaunchKernelGGL(inertia_kernel, dim3(unsigned(blocks)), dim3(64 * kInertiaWaves), 0, s, a, chunk);
   }
   SweepArgs b = a;

@@ -59,7 +59,6 @@ namespace {
 using inertia::Tally;
 using inertia::wave_sum;
 
-constexpr int kInertiaWaves = 4;        // wavefronts per workgroup
 constexpr int kDeferredIdx = -0x4d;     // idx of a deferred wavelength between the two launches
 constexpr int kTrySpacing = 100;        // grid steps between points, at most, for the Try stage
 

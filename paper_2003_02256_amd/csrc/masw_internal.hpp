@@ -125,10 +125,11 @@ struct SweepArgs {
   double* misfit;             // [n_models]
   int32_t* model_left;        // [n_models] wavelengths not finished (set by the staging)
   const int32_t* lambda_off;  // [n_models + 1]
-  // Work counts of each workgroup, [gridDim.x][kWgCounts] (plain stores; the
+  // Work counts of each workgroup, [wg_rows][kWgCounts] (plain stores; the
   // host sums them for masw_get_stats): one atomic add per workgroup and
   // counter on a shared cache line serialises at the end of a launch.
   unsigned long long* wg_counts;
+  int32_t wg_rows;  // rows of wg_counts: a launch that would write more is refused
   // A small single-model launch with the staging folded in (fused != 0, one
   // item per workgroup, the item of workgroup w is wavelength w): each
   // workgroup checks the raw model and grid itself, builds the model's layer
@@ -153,6 +154,26 @@ constexpr int kFusedMaxLayers = 64;     // layers of a model that a fused launch
 constexpr int kFusedMaxGrid = 16384;    // grid points that each workgroup of a fused launch checks
 constexpr int kWgCounts = 8;  // sweep, check, refine, useful, helper, inertia evals, entries, pivots
 constexpr int kMaxWgRows = 65536;  // workgroup rows reserved for wg_counts (above any launch's grid)
+
+// Rows of wg_counts reserved for a call.  No launch has more workgroups than
+// wavelengths: the sweeps take at most one workgroup per item, the staged picks
+// and the persistent inertia search have a fixed number per CU and run only
+// above it, and lone_blocks is below.
+__host__ __device__ constexpr int64_t wg_rows_of(int64_t n_lam) {
+  return n_lam < 1 ? 1 : n_lam < kMaxWgRows ? n_lam : kMaxWgRows;
+}
+
+// The inertia search by S lanes a wavelength (masw_inertia_lone.hip):
+// wavefronts per workgroup, and wavefronts for the parts of runs that further
+// models begin (one a model while there are no more models than wavelengths).
+constexpr int kInertiaWaves = 4;
+__host__ __device__ constexpr int64_t lone_runs(int64_t n_items, int S) { return (n_items + 64 / S - 1) / (64 / S); }
+__host__ __device__ constexpr int64_t lone_extra(int64_t n_items, int64_t n_models, int S) {
+  return S == 64 || n_models < 2 ? 0 : n_models < n_items ? n_models : n_items;
+}
+__host__ __device__ constexpr int64_t lone_blocks(int64_t n_items, int64_t n_models, int S) {
+  return (lone_runs(n_items, S) + lone_extra(n_items, n_models, S) + kInertiaWaves - 1) / kInertiaWaves;
+}
 
 // Zero-state of the cooperative arrays (one launch before the sweep).
 struct CoopInitArgs {

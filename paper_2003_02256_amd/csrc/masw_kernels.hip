@@ -675,7 +675,7 @@ int sweep_blocks_per_cu(int mode, int G) {
 
 hipError_t launch_sweep(int mode, int G, int blocks, hipStream_t s, const SweepArgs& a) {
   const void* f = sweep_symbol(mode, G, a.misfit != nullptr);
-  if (!f) return hipErrorInvalidValue;
+  if (!f || blocks > a.wg_rows) return hipErrorInvalidValue;
   void* args[] = {const_cast<SweepArgs*>(&a)};
   return hipLaunchKernel(f, dim3(blocks), dim3(64 * G), args, 0, s);
 }
@@ -683,7 +683,7 @@ hipError_t launch_sweep(int mode, int G, int blocks, hipStream_t s, const SweepA
 hipError_t launch_fused(int mode, int blocks, hipStream_t s, const SweepArgs& a) {
   const void* f = mode == kModeFP64 ? reinterpret_cast<const void*>(&fused_sweep_kernel<kModeFP64>)
                                     : split_fused_symbol();
-  if (!f || a.fused_N < 0 || a.fused_N > kFusedMaxLayers) return hipErrorInvalidValue;
+  if (!f || a.fused_N < 0 || a.fused_N > kFusedMaxLayers || blocks > a.wg_rows) return hipErrorInvalidValue;
   void* args[] = {const_cast<SweepArgs*>(&a)};
   return hipLaunchKernel(f, dim3(blocks), dim3(64 * kFusedG), args, unsigned(fused_lds_bytes(a.fused_N)), s);
 }

@@ -235,6 +235,7 @@ hipError_t launch(int cus, hipStream_t s, const SweepArgs& a, int* blocks_out, i
   const int picking = int(std::min<int64_t>((runs + 3) / 4, int64_t(cus) * 4)), rest = cus * 16;
   *blocks_out = blocks;
   *rows = blocks + 4 * picking + rest;
+  if (*rows > a.wg_rows) return hipErrorInvalidValue;
   SweepArgs b = a;
   hipLaunchKernelGGL(first_change_kernel<MODE>, dim3(blocks), dim3(64), 0, s, b);
   b.wg_counts += size_t(blocks) * kWgCounts;

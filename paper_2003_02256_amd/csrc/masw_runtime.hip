@@ -121,14 +121,10 @@ struct Inputs {
 // Blocks of the grid check, one flag each.
 size_t grid_blocks(int64_t n_c) { return size_t((n_c + kPrepThreads - 1) / kPrepThreads); }
 
-// Rows of per-workgroup work counts a launch may write: one per workgroup,
-// and a launch has at most one workgroup per wavelength.
-size_t wg_rows(const Inputs& in) {
-  return size_t(std::min<int64_t>(std::max<int64_t>(in.n_lam, 1), kMaxWgRows));
-}
+// Rows of per-workgroup work counts a launch may write.
+size_t wg_rows(const Inputs& in) { return size_t(wg_rows_of(in.n_lam)); }
 
 // Total device bytes of one call's workspace.
-
 size_t workspace_bytes(const Inputs& in, bool stage_inputs, bool stage_outputs) {
   Bump b{nullptr, ~size_t(0), 0};
   const size_t R = size_t(in.n_layers_total + in.n_models);
@@ -364,6 +360,7 @@ int run_curves(masw_ctx* ctx, const Inputs& in, masw_precision prec, uint32_t fl
     p.misfit = misfit_dev;
   }
   sw.wg_counts = b.take<unsigned long long>(wg_rows(in) * kWgCounts);
+  sw.wg_rows = int32_t(wg_rows(in));
   if (!b.ok()) return fail(MASW_ENOMEM, "workspace exceeds the HBM budget");
 
   const bool inertia = (flags & MASW_SEARCH_INERTIA) != 0;
