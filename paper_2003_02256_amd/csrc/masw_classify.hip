@@ -79,7 +79,6 @@ constexpr int kGroups = 64 / kGroup;        // wavelengths per wavefront
 constexpr int kMaxStepsPerLayer = 1 << 16;  // beyond this a layer is not crossed
 constexpr int kMaxRounds = 4;               // of a pick's eight lanes, before it is deferred
 constexpr int kMaxWideRounds = 8;           // of a deferred pick's 64 lanes: 63^8 > 2e14
-constexpr int kDeferred = -2;               // a deferred pick's class between the two launches
 constexpr int kTerms = 12;                  // series terms, |U|, |W| <= 1
 constexpr double kRootTol = 1e-12;
 
@@ -311,9 +310,10 @@ struct LaneWork {
   int N;
 };
 
-// Wavelength wl as eight lanes (`sub` the lane among them) see it: its model,
-// k and bracket, and its class where no evaluation is needed, else -1.
-__device__ int lane_work(const ClassifyArgsDev& a, int64_t wl, int sub, unsigned long long group, LaneWork* o) {
+// Wavelength wl with bracket index i as eight lanes (`sub` the lane among them)
+// see it: its model, k and bracket, and its class where no evaluation is
+// needed, else -1.
+__device__ int lane_work(const ClassifyArgsDev& a, int64_t wl, int i, int sub, unsigned long long group, LaneWork* o) {
   // model of wavelength wl: lambda_off[m] <= wl < lambda_off[m + 1]
   int m_lo = 0, m_hi = a.n_models;
   while (m_hi - m_lo > 1) {
@@ -328,7 +328,6 @@ __device__ int lane_work(const ClassifyArgsDev& a, int64_t wl, int sub, unsigned
   o->be = a.beta + r0;
   o->rh = a.rho + r0;
   o->N = N;
-  const int i = a.idx[wl];
   if (i < 1 || i >= a.n_c) return MASW_PICK_NONE;
   // device validation of the model, the wavelength and the bracket
   bool bad = (N < 0 || N > MASW_MAX_LAYERS);
@@ -424,17 +423,19 @@ __global__ __launch_bounds__(64 * kClassifyWaves) void classify_kernel(ClassifyA
   unsigned rounds = 0, steps = 0;
   LaneWork w{};
   int cls = MASW_PICK_NONE;
-  if (wl < a.n_lam) cls = lane_work(a, wl, sub, group, &w);
+  const int idx = wl < a.n_lam ? a.idx[wl] : 0;
+  if (wl < a.n_lam) cls = lane_work(a, wl, idx, sub, group, &w);
   double root = __builtin_nan("");
   const unsigned long long todo = __ballot(cls < 0);
   if (todo != 0ull) {
     // lanes without an evaluation of their own mirror the first that has one
     const int src = __ffsll((long long)todo) - 1;
     const int64_t wl_src = __shfl(wl, src, 64);
+    const int idx_src = __shfl(idx, src, 64);
     bool done = cls >= 0;
     if (done) {
       LaneWork o{};
-      (void)lane_work(a, wl_src, sub, group, &o);
+      (void)lane_work(a, wl_src, idx_src, sub, group, &o);
       w = o;
     }
     const double tol = kRootTol * w.c_hi;
@@ -490,7 +491,7 @@ __global__ __launch_bounds__(64 * kClassifyWaves) void classify_kernel(ClassifyA
           } else if (round == 0) {
             est = __builtin_fma(span, t * (1.0 / 7.0), w.c_lo);
           } else if (l == 0 || l == kGroup || round == kMaxRounds - 1) {
-            cls = kDeferred;
+            cls = -idx;  // deferred (idx and pick_class may be one array)
             done = true;
           } else {
             const double q = __builtin_ldexp(F_hi.mant / F_lo.mant, max(-1000, min(1000, F_hi.expo - F_lo.expo)));
@@ -509,7 +510,7 @@ __global__ __launch_bounds__(64 * kClassifyWaves) void classify_kernel(ClassifyA
   add_counts(a, s_cnt, 64ull * rounds, rounds * (unsigned long long)unsigned(max(w.N, 0)), steps);
 }
 
-// The deferred picks, one whole wavefront each: multisection with 64 equally
+// The deferred picks (class -idx), one whole wavefront each: multisection with 64 equally
 // spaced points a round, the first whose sign differs from the lower end's
 // giving the next bracket, 63 times narrower.  A wavefront looks through
 // every gridDim-th pick, so that neighbouring picks, which are often deferred
@@ -523,11 +524,13 @@ __global__ __launch_bounds__(64 * kClassifyWaves) void classify_deferred_kernel(
   unsigned steps = 0;
   for (int64_t base = first; base < a.n_lam; base += 64 * n_waves) {
     const int64_t mine = base + lane * n_waves;
-    unsigned long long todo = __ballot(mine < a.n_lam && a.cls[mine < a.n_lam ? mine : 0] == kDeferred);
+    const int marked = mine < a.n_lam ? a.cls[mine] : 0;
+    unsigned long long todo = __ballot(marked < 0);
     for (; todo != 0ull; todo &= todo - 1) {
-      const int64_t wl = base + (__ffsll((long long)todo) - 1) * n_waves;
+      const int from = __ffsll((long long)todo) - 1;
+      const int64_t wl = base + from * n_waves;
       LaneWork w{};
-      (void)lane_work(a, wl, lane & (kGroup - 1), ~0ull, &w);
+      (void)lane_work(a, wl, -__shfl(marked, from, 64), lane & (kGroup - 1), ~0ull, &w);
       const double tol = kRootTol * w.c_hi;
       const double c2_lo = w.c_lo * w.c_lo, c2_hi = w.c_hi * w.c_hi;
       double lo = w.c_lo, hi = w.c_hi;
