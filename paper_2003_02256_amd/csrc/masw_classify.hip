@@ -47,8 +47,10 @@
 // the search in two rounds, 16 evaluations, and an estimate off by a rung or
 // two narrows the bracket to that rung, with linear interpolation for the
 // next round.  A root beyond the ladder, or not reached in kMaxRounds (a grid
-// step of many m/s, several roots in one step), is deferred to a second
-// launch, in which a whole wavefront multisects it with 64 points a round.
+// step of many m/s), and a step in which the polynomial has several roots, are
+// deferred to a second launch, in which a whole wavefront multisects with 64
+// points a round, so that of several roots it finds the first that 64 points
+// show.
 // For the interpolation F is the analytic dispersion function: the
 // orthonormalisations' divisors are multiplied back in, and each layer is cut
 // into the same number of steps at every point of a bracket (the larger of
@@ -350,8 +352,10 @@ __device__ int lane_work(const ClassifyArgsDev& a, int64_t wl, int i, int sub, u
 // Root, in units of the spacing from the first point, of the polynomial
 // through the group's eight values at equally spaced points, between points
 // l - 1 and l where the sign changes: forward differences and secant steps
-// on Newton's form.
-__device__ double poly_root(const Secular& v, int l) {
+// on Newton's form.  *changes receives the polynomial's sign changes among 64
+// equally spaced points (the eight among them): a pair of roots between two of
+// the eight points leaves no trace in their signs.
+__device__ double poly_root(const Secular& v, int l, int* changes) {
   int top = v.expo;  // the values at one common exponent, the largest
 #pragma unroll
   for (int off = kGroup / 2; off >= 1; off >>= 1) top = max(top, __shfl_xor(top, off, kGroup));
@@ -365,12 +369,32 @@ __device__ double poly_root(const Secular& v, int l) {
   for (int n = 1; n < kGroup; ++n)
 #pragma unroll
     for (int i = kGroup - 1; i >= n; --i) d[i] -= d[i - 1];
+  constexpr double kInv[kGroup] = {1.0, 1.0, 1.0 / 2, 1.0 / 6, 1.0 / 24, 1.0 / 120, 1.0 / 720, 1.0 / 5040};
+#pragma unroll
+  for (int n = 2; n < kGroup; ++n) d[n] *= kInv[n];
+  auto newton_form = [&](double t) {
+    double p = d[kGroup - 1];
+#pragma unroll
+    for (int n = kGroup - 2; n >= 0; --n) p = __builtin_fma(p, t - double(n), d[n]);
+    return p;
+  };
+  int sub = int(threadIdx.x) & (kGroup - 1);
+  asm volatile("" : "+v"(sub));  // (the points would otherwise be held in registers over the rounds)
+  int n_changes = 0;  // of points 8 sub .. 8 sub + 8 (63 at most) of the 64, spaced 1/9
+  bool up = newton_form(double(8 * sub) * (1.0 / 9.0)) > 0.0;
+#pragma unroll 1
+  for (int i = 1; i <= 8; ++i) {
+    const bool next = newton_form(double(min(8 * sub + i, 63)) * (1.0 / 9.0)) > 0.0;
+    n_changes += next != up ? 1 : 0;
+    up = next;
+  }
+#pragma unroll
+  for (int off = kGroup / 2; off >= 1; off >>= 1) n_changes += __shfl_xor(n_changes, off, kGroup);
+  *changes = n_changes;
   const double a = t0, b = t1;
   double t = t0 - f0 * (t1 - t0) / (f1 - f0);
   for (int it = 0; it < 4; ++it) {
-    double p = d[kGroup - 1];
-#pragma unroll
-    for (int n = kGroup - 2; n >= 0; --n) p = __builtin_fma(p * (t - double(n)), 1.0 / double(n + 1), d[n]);
+    const double p = newton_form(t);
     // secant step from the end of the pair that is nearer in value
     if (__builtin_fabs(f1) < __builtin_fabs(f0)) {
       t0 = t1;
@@ -412,7 +436,7 @@ __device__ void add_counts(const ClassifyArgsDev& a, unsigned long long (*s_cnt)
   }
 }
 
-__global__ __launch_bounds__(64 * kClassifyWaves) void classify_kernel(ClassifyArgsDev a) {
+__global__ __launch_bounds__(64 * kClassifyWaves) __attribute__((amdgpu_waves_per_eu(3))) void classify_kernel(ClassifyArgsDev a) {
   __shared__ unsigned long long s_cnt[kClassifyWaves][3];
   const int lane = int(threadIdx.x) & 63;
   const int wave = int(threadIdx.x) >> 6;
@@ -467,13 +491,17 @@ __global__ __launch_bounds__(64 * kClassifyWaves) void classify_kernel(ClassifyA
       const double c_l = __shfl(cl, l & 7, kGroup), c_b = __shfl(cl, (l - 1) & 7, kGroup);
       const Secular F_l{__shfl(F.mant, l & 7, kGroup), __shfl(F.expo, l & 7, kGroup)};
       const Secular F_b{__shfl(F.mant, (l - 1) & 7, kGroup), __shfl(F.expo, (l - 1) & 7, kGroup)};
-      const double t = round == 0 ? poly_root(F, l < 1 || l > 7 ? 1 : l) : 0.0;
+      int changes = 1;
+      const double t = round == 0 ? poly_root(F, l < 1 || l > 7 ? 1 : l, &changes) : 0.0;
       if (!done) {
         if (nans) {
           cls = MASW_PICK_UNRESOLVED;
           done = true;
         } else if (round == 0 && s_last == s_lo) {
           cls = MASW_PICK_POLE;
+          done = true;
+        } else if (changes != 1) {  // several roots, perhaps: the first among 64 points, as below
+          cls = -idx;
           done = true;
         } else {
           if (l > 0) {
