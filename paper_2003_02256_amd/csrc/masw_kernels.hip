@@ -552,7 +552,7 @@ void tick_kernel(TickArgs a) {
     r.c32 = sd.c32;
     r.L64 = as_global(sd.L64);
     r.L32 = as_global(sd.L32);
-    r.c_low = minors_from(r.L64, r.N);
+    r.low = r.c64[0] < minors_from(r.L64, r.N) ? 1 : 0;
     const int og = sd.out_base + j;
     const ItemOut o{a.out_ct + og, a.out_idx + og, a.out_status + og, a.out_cref + og,
                     (a.refine && !(sd.flags & MASW_NO_REFINE)) ? 1 : 0, a.refine_rel};

@@ -61,7 +61,7 @@ void first_change_kernel(SweepArgs a) {
       const float k32 = float(r.k64);
       int carry = kNoSign, found = -1, sig_f, prev_f;
       // (a grid that starts below c_low is left to the last launch)
-      const bool low = MODE == kModeFP64 && r.c64[0] < r.c_low;
+      const bool low = MODE == kModeFP64 && r.low;
       for (int base = 0; base < n && !low; base += 64) {
         const int i = base + lane;
         int sg = kNoSign;
