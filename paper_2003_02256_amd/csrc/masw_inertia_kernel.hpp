@@ -28,9 +28,9 @@
 //           cubic interpolation of det K names the grid step of the change.
 //           Round 0 of the refinement (masw_pick.hpp) is evaluated on it (on
 //           the S / 8 steps around it): its first and last points are the
-//           step's ends, so E = 0 at the one and sign(det K) < 0 at the other
-//           settle the pick and start its refinement at once.  Otherwise they
-//           narrow the bracket.
+//           step's ends, so E = 0 at the one and E = 1 at the other settle the
+//           pick, prove that the step holds a single root and no pole, and start
+//           its refinement at once.  Otherwise they narrow the bracket.
 //   Refine: the further rounds of the refinement, then the outputs.
 // So a wavelength whose pick is predicted takes three rounds of eight: 24
 // evaluations, where 64 lanes a wavelength took about 65 counts and 128
@@ -38,7 +38,7 @@
 //
 // A wavelength is left to the search of masw_inertia.hpp by a whole wavefront
 // where E(c_test[0]) is not 0, the grid step of the change holds a pole or
-// several changes, or its upper end is at or above the half-space's S
+// several roots, or its upper end is at or above the half-space's S
 // velocity.  With S = 64 or 32 the wavefront runs it at once;
 // else a second launch does (deferred picks: idx = kDeferredIdx in between),
 // so that many of one wavefront's are shared out.
@@ -89,34 +89,48 @@ __device__ __forceinline__ void run_wavelength(const SweepArgs& a, int g, Tally&
 }
 
 // One grid or refinement point: det_sign's sign and value m 2^e, whether
-// E(c) = 0, and whether some layer denominator is negative.
+// E(c) = 0 and, where `ask`, whether E(c) = 1 (inertia::count_E; an event is
+// neither).  With COUNT, E(c) itself (kEvent where it has none) and the two, all
+// only where `ask`, and whether some layer denominator is negative.
 struct Point {
   double m;
   int e, sg;
-  bool zero, pole;
+  bool zero, one;
+  int E;
+  bool pole;
 };
 
-__device__ __forceinline__ Point eval_point(double c, double k, const LayerRec64* __restrict__ L, int N) {
+template <bool COUNT>
+__device__ __forceinline__ Point eval_point(double c, double k, const LayerRec64* __restrict__ L, int N,
+                                            bool ask) {
   const double c2 = c * c;
   Block2<double> S{0.0, 0.0, 0.0};
-  bool neg = false, definite = true, bounded = true;
+  // (what is tracked over the layers is one mask and otherwise vector registers:
+  // masks that do not fit the scalar registers are moved at every layer)
+  int odd = 0;             // negative pivot determinants
+  bool good = true;        // no pivot with both eigenvalues negative
+  int s = 0;               // COUNT: negative eigenvalues
+  double x_min = 1.0;      // smallest (k h)^2 (1 - c^2/beta^2)
   Point o;
   o.pole = false;
   double m = 1.0;
   int e = 0;
+  auto pivot = [&](double a, double d) {  // (1,1) entry and determinant
+    odd += d < 0.0 ? 1 : 0;
+    if constexpr (COUNT) s += inertia::neg_eigs(a, d);
+    else good = good && (a > 0.0 || d < 0.0);
+  };
   LayerRec<double> nxt = load_rec<double>(L, 0);
   for (int j = 0; j < N; ++j) {
     const LayerRec<double> rec = nxt;
     nxt = load_rec<double>(L, j + 1);  // one layer ahead; after the last layer, the half-space
     const double kh = k * rec.h;
     const LayerK<double> K = layer_entries<double>(c2, kh, rec.ia2, rec.ib2, rec.rh, rec.mh);
-    o.pole = o.pole || K.gD < 0.0;
+    if constexpr (COUNT) o.pole = o.pole || K.gD < 0.0;
     const double a = S.s11 + K.k11;
     const double d = schur_layer<double>(S, K);
-    neg ^= (d < 0.0);
-    definite = definite && a > 0.0 && d > 0.0 && d < __builtin_inf();
-    // layer_poles' bound k h sqrt(c^2/beta^2 - 1) < pi, with det_sign_inertia's margin
-    bounded = bounded && kh * kh * (1.0 - c2 * rec.ib2) > -9.86;
+    pivot(a, d);
+    x_min = __builtin_fmin(x_min, kh * kh * (1.0 - c2 * rec.ib2));
     int ex;
     m = __builtin_frexp(m * d, &ex);
     e += ex;
@@ -124,20 +138,24 @@ __device__ __forceinline__ Point eval_point(double c, double k, const LayerRec64
   const LayerRec<double> hs = nxt;
   double re, im, ar;
   halfspace_det<double>(S, c2, hs.ia2, hs.ib2, hs.mh, &re, &im, &ar);
-  definite = definite && ar > 0.0 && re > 0.0 && re < __builtin_inf() && c2 * hs.ib2 < 1.0;
+  o.sg = sign_code((odd & 1) != 0, re);
+  pivot(ar, re);
   int ex;
   o.m = __builtin_frexp(m * re, &ex);
   o.e = e + ex;
-  o.sg = sign_code(neg, re);
-  // rare: no negative eigenvalue, but a layer above its energy bound, whose
-  // sublayers have to be counted
-  o.zero = definite && bounded;
-  const bool count = definite && !bounded;
-  if (__ballot(count) != 0ull && count) {
-    bool ok = true;
-    const int P = inertia::poles_below(c, k, L, N, &ok);
-    o.zero = ok && P == 0;
-  }
+  // (a pivot's determinant that is zero or not finite stays in the product)
+  good = good && o.m != 0.0 && __builtin_fabs(o.m) < __builtin_inf() && c2 * hs.ib2 < 1.0;
+  // layer_poles' bound k h sqrt(c^2/beta^2 - 1) < pi, with det_sign_inertia's margin
+  const bool bounded = x_min > -9.86;
+  if constexpr (!COUNT) s = odd;
+  // rare: a layer above its energy bound, whose sublayers have to be counted
+  int P = 0;
+  const bool count = good && !bounded && (COUNT ? ask : s == 0 || (ask && s == 1));
+  if (__ballot(count) != 0ull && count) P = inertia::poles_below(c, k, L, N, &good);
+  good = good && (bounded || count);
+  o.E = good ? s + 2 * P : inertia::kEvent;
+  o.zero = o.E == 0;
+  o.one = o.E == 1;
   return o;
 }
 
@@ -160,7 +178,6 @@ __device__ __forceinline__ void run_groups(const SweepArgs& a, int begin, int en
   const int N = __builtin_amdgcn_readfirstlane(d.n_layers), n_c = __builtin_amdgcn_readfirstlane(d.n_c);
   const double* c64 = a.c64 + __builtin_amdgcn_readfirstlane(d.c_base);
   const LayerRec64* L = a.layers64 + __builtin_amdgcn_readfirstlane(d.layer_base);
-  const double ib2_hs = load_rec<double>(L, N).ib2;
   const int per = (end - begin + kGroups - 1) / kGroups;
   int g = begin + (lane / S) * per;
   const int g_end = min(g + per, end);
@@ -221,13 +238,11 @@ __device__ __forceinline__ void run_groups(const SweepArgs& a, int begin, int en
         c = __builtin_fma(c - c_b, double(sub & 7) * (1.0 / 7.0), c_b);
       }
     }
-    const Point v = eval_point(c, k, L, N);
+    const Point v = eval_point<false>(c, k, L, N, live && stage == kTry && (sub & 7) == 7);
     const unsigned n_search = __popcll(__ballot(live && stage < kRefine && valid));
     rounds.evals += n_search;
     rounds.entries += (unsigned long long)n_search * unsigned(N);
     rounds.refine += __popcll(__ballot(live && stage == kRefine && sub < 8));
-
-    const int sg_prev = previous_lane(v.sg);
 
     // the search stages' outcome: next stage, or a wavelength's end
     int end_as = 0;  // 1: no pick, 2: deferred, 3: picked
@@ -274,12 +289,10 @@ __device__ __forceinline__ void run_groups(const SweepArgs& a, int begin, int en
         lo = last_step;
       } else {
         const int q = base + (f & ~7);  // its step's eight lanes
-        const unsigned long long mine = 0xffull << (f & ~7);
-        const unsigned changes = unsigned(__popcll(in_group((sub & 7) > 0 && v.sg != sg_prev) & mine));
         const double c_lo = from_lane<U>(c, q), c_hi = from_lane<U>(c, q + 7);
         hi = from_lane<U>(p, q);
-        if ((f & 7) == 0 || from_lane<U>(v.sg, q + 7) != -1 || (in_group(v.pole) & mine) != 0ull || changes > 1u ||
-            !(c_hi * c_hi * ib2_hs < 1.0)) {
+        // E = 0 and E = 1 at the step's ends: a mode lies between them and nothing else
+        if ((f & 7) == 0 || (in_group(v.one) >> (f & ~7) & 0x80ull) == 0ull) {
           end_as = 2;
         } else {
           located = true;

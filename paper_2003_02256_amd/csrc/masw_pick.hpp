@@ -198,22 +198,36 @@ struct Refine8 {
 
 // Status, refined root and outputs of the pick at grid index `found`, whose
 // determinant signs are sig_f there and prev_f at found - 1.  Run by one whole
-// wavefront, every eight lanes of which repeat the eight points of a Refine8
-// of [c[found-1], c[found]]; its lane 0 stores the outputs.  The first round
-// also yields the layer-denominator sign masks at the two grid points (pole
-// flag).  Where the masks of its points differ or the sign changes more than
-// once among them (a pole in the step, perhaps with zeros beside it),
-// multisection of the whole step takes Refine8's place: 64 increasing points
-// per round, one per lane, lanes 0 and 63 at the bracket's ends; the new
+// wavefront, whose lane 0 stores the outputs.  The first round takes 64 equally
+// spaced points of the step: the eight of a Refine8 in lanes 0..7 and the 56
+// between them, in order, in lanes 8..63.  It yields the layer-denominator sign
+// masks at the two grid points (pole flag), and where the masks of all its
+// points are the same and the sign changes once, the refinement goes on with
+// the eight.  Otherwise (a pole in the step, perhaps with zeros beside it, or
+// several zeros) multisection of the whole step takes its place: 64 increasing
+// points per round, one per lane, lanes 0 and 63 at the bracket's ends; the new
 // bracket is the first sign change.  A uniform round (63 equal parts) is
 // followed by at most one window round: linear interpolation of det K (of
 // 1/det K at a pole) between the new bracket's ends estimates the root, and
 // lanes 1..62 are placed 0.9 tol apart around the estimate.
-// Returns the determinant evaluations made (8 or 64 a round).
+// Returns the determinant evaluations made (64 in the first round and in those
+// of the multisection, else 8).
 // With `confirm` the signs are a sweep's (masw_secular.hpp), and the
 // determinant's own at the two grid points, which the first round evaluates,
 // have the last word: kUnconfirmed is added, and nothing written, where they
 // show no change.
+
+// Whether the signs of 64 points that rise through lanes 0, 8..15, 1, 16..23,
+// 2, ..., 56..63, 7 are those of one change: `differ` has the lanes whose sign
+// differs from the first point's.
+__device__ __forceinline__ bool one_change(unsigned long long differ) {
+  const unsigned long long a = differ & 0xffull, b = differ >> 8;
+  const int f = a ? __ffsll((long long)a) - 1 : 8, t = b ? __ffsll((long long)b) - 1 : 56;
+  // both rise once, and the first of the 56 lies in the eight's interval f - 1
+  return f >= 1 && f < 8 && (a >> f) + 1ull == 1ull << (8 - f) && (b >> t) + 1ull == 1ull << (56 - t) &&
+         t >= 8 * (f - 1) && t <= 8 * f;
+}
+
 constexpr unsigned long long kUnconfirmed = 1ull << 63;
 __device__ __forceinline__ unsigned long long refine_and_write(const ItemOut& o, const double* c64, double k64,
                                                                const LayerRec64* L64, int N, int found, int sig_f,
@@ -233,7 +247,11 @@ __device__ __forceinline__ unsigned long long refine_and_write(const ItemOut& o,
       int lane = threadIdx.x & 63;
       asm volatile("" : "+v"(lane));
       double c;
-      if (r.stage < kUniform64) {
+      if (k == 0) {
+        // (n, of 63 equal parts; every ninth is one of the eight, and rounded as it is)
+        const int n = lane - 7 + (lane >> 3) - 1;
+        c = lane < 8 ? r.point(lane) : __builtin_fma(r.hi - r.lo, double(n) * (1.0 / 63.0), r.lo);
+      } else if (r.stage < kUniform64) {
         c = r.point(lane & 7);
       } else if (r.stage == kWindow64) {
         const double step = 0.9 * r.tol;  // window spacing
@@ -248,7 +266,7 @@ __device__ __forceinline__ unsigned long long refine_and_write(const ItemOut& o,
       const int sg = det_sign_value(c, k64, L64, N, &dm, &mant, &expo);
       int s_c = 0, p_c = 0, unused;
       if (r.stage < kUniform64) {
-        evals += 8ull;
+        evals += k == 0 ? 64ull : 8ull;
         if (k == 0) {
           if (confirm) {
             const int s_lo = from_lane<true>(sg, 0), s_hi = from_lane<true>(sg, 7);
@@ -259,8 +277,8 @@ __device__ __forceinline__ unsigned long long refine_and_write(const ItemOut& o,
           const unsigned long long other = __ballot(dm != dm_lo);
           if (other >> 7 & 1ull) status |= MASW_FLAG_POLE;
           if (!o.refine) break;
-          const int prev = previous_lane(sg);
-          if (other != 0ull || __popcll(__ballot((lane & 7) > 0 && sg != prev) & 0xffull) > 1) {
+          const int s_first = from_lane<true>(sg, 0);
+          if (other != 0ull || __ballot(sg == kNaNSign) != 0ull || !one_change(__ballot(sg != s_first))) {
             r.stage = kUniform64;
             continue;
           }

@@ -19,8 +19,8 @@
 //       first round has K's own signs at the pick's two grid points.
 //   pick_rest_kernel: the others (no change found in FP32, a grid that starts
 //       below c_low, a candidate that the eight points do not settle, a pole in
-//       the step or several changes, a change that the elimination does not
-//       confirm), by a whole wavefront each, as the one-launch sweep does them
+//       the step or several changes of E, a step at or above the half-space's S
+//       velocity, a change that the elimination does not confirm), by a whole wavefront each, as the one-launch sweep does them
 //       from the candidate on.
 // Between the launches out_idx holds the candidate, or kDeferredIdx with the
 // candidate (-1: none) in out_status.  Indices, statuses and roots are those
@@ -129,7 +129,7 @@ __device__ __forceinline__ void run_picks(const SweepArgs& a, int begin, int end
     }
     if (__ballot(live) == 0ull) break;
     const double c = check ? c64[min(first + sub, n_c - 1)] : r.point(sub);
-    const Point v = eval_point(c, k, L, N);
+    const Point v = eval_point<true>(c, k, L, N, live && (check || (r.stage == 0 && r.round == 0)));
     const int sg_prev = previous_lane(v.sg);
     const unsigned above = in_group(!v.zero), pole = in_group(v.pole);
     const unsigned changes = in_group(sub > 0 && v.sg != sg_prev), nan = in_group(v.sg == kNaNSign);
@@ -144,8 +144,11 @@ __device__ __forceinline__ void run_picks(const SweepArgs& a, int begin, int end
       r.init(c_lo, c_hi, a.refine_rel);
       check = false;
     } else if (live) {
+      // one change of E over the step, and no pole: a single root
       const int s_lo = from_lane<false>(v.sg, base), s_hi = from_lane<false>(v.sg, base + 7);
-      if (r.stage == 0 && r.round == 0 && (pole != 0u || nan != 0u || s_lo == s_hi || __popc(changes) > 1))
+      const int E_lo = from_lane<false>(v.E, base), E_hi = from_lane<false>(v.E, base + 7);
+      if (r.stage == 0 && r.round == 0 &&
+          (pole != 0u || nan != 0u || s_lo == s_hi || E_hi == inertia::kEvent || E_hi != E_lo + 1))
         rest = true;
       else
         done = r.update(c, v.sg, v.m, v.e, base) || !a.refine;

@@ -49,3 +49,24 @@ def test_classified_root_is_the_first(ctx, m, lam, step, roots):
         cls, sec = ctx.classify(c, [m], [np.full(copies, lam)], np.ones(copies, np.int32))
         assert np.all(cls == M.MASW_PICK_MODE)
         assert np.all(np.abs(sec - want) <= 1e-9 * want), (sec, want)
+
+
+# Every form of the sweep and of the inertia search: alone (a fused launch), in
+# staged launches of 5000 and of 49,153 wavelengths and more (the sweep and the
+# picks apart), and 64, 32 and 8 lanes a wavelength.
+@pytest.mark.parametrize("search", ["walk", "split", "inertia"])
+@pytest.mark.parametrize("copies", [1, 2100, 5000, 33000, 60000])
+def test_refined_root_is_the_first(ctx, search, copies):
+    prec = M.MASW_PREC_SPLIT if search == "split" else M.MASW_PREC_FP64
+    flags = M.MASW_SEARCH_INERTIA if search == "inertia" else 0
+    for m, lam, step, roots in CASES:
+        alone = np.array([roots[0] - 0.1, roots[0] + 0.1])
+        want = PR.classify(lam, alone, 1, m)[1]
+        n = 1100 if search == "split" else 30      # a split call on fewer points is the FP64 walk
+        c = np.r_[np.linspace(120.0, step[0], n), step[1], step[1] + 1.0 + np.arange(5.0)]
+        if copies == 1:
+            ct, idx, st, ref = ctx.curve(c, np.array([lam]), m, prec, flags)
+        else:
+            ct, idx, st, ref = ctx.batch(c, [m], [np.full(copies, lam)], prec, flags)
+        assert np.all(idx == n) and np.all(ct == step[1]) and np.all(st == M.MASW_STATUS_FOUND)
+        assert np.all(np.abs(ref - want) <= 2e-9 * want), (ref[:3], want)
