@@ -90,14 +90,13 @@ __device__ __forceinline__ void run_wavelength(const SweepArgs& a, int g, Tally&
 
 // One grid or refinement point: det_sign's sign and value m 2^e, whether
 // E(c) = 0 and, where `ask`, whether E(c) = 1 (inertia::count_E; an event is
-// neither).  With COUNT, E(c) itself (kEvent where it has none) and the two, all
-// only where `ask`, and whether some layer denominator is negative.
+// neither).  With COUNT, E(c) itself (kEvent where it has none) and the poles
+// counted in it, both only where `ask`.
 struct Point {
   double m;
   int e, sg;
   bool zero, one;
-  int E;
-  bool pole;
+  int E, P;
 };
 
 template <bool COUNT>
@@ -112,7 +111,6 @@ __device__ __forceinline__ Point eval_point(double c, double k, const LayerRec64
   int s = 0;               // COUNT: negative eigenvalues
   double x_min = 1.0;      // smallest (k h)^2 (1 - c^2/beta^2)
   Point o;
-  o.pole = false;
   double m = 1.0;
   int e = 0;
   auto pivot = [&](double a, double d) {  // (1,1) entry and determinant
@@ -126,7 +124,6 @@ __device__ __forceinline__ Point eval_point(double c, double k, const LayerRec64
     nxt = load_rec<double>(L, j + 1);  // one layer ahead; after the last layer, the half-space
     const double kh = k * rec.h;
     const LayerK<double> K = layer_entries<double>(c2, kh, rec.ia2, rec.ib2, rec.rh, rec.mh);
-    if constexpr (COUNT) o.pole = o.pole || K.gD < 0.0;
     const double a = S.s11 + K.k11;
     const double d = schur_layer<double>(S, K);
     pivot(a, d);
@@ -153,6 +150,7 @@ __device__ __forceinline__ Point eval_point(double c, double k, const LayerRec64
   const bool count = good && !bounded && (COUNT ? ask : s == 0 || (ask && s == 1));
   if (__ballot(count) != 0ull && count) P = inertia::poles_below(c, k, L, N, &good);
   good = good && (bounded || count);
+  o.P = P;
   o.E = good ? s + 2 * P : inertia::kEvent;
   o.zero = o.E == 0;
   o.one = o.E == 1;

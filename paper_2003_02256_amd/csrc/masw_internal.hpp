@@ -62,7 +62,7 @@ struct alignas(64) Counters {
   uint32_t tick_exit;         // serving: workgroups that have left their tick (never cleared)
   uint32_t deferred;          // inertia search: wavefronts that left wavelengths to the second launch;
                               // staged picks: wavelengths left to the last launch
-  uint32_t rest_head;         // staged picks: the next of them
+  uint32_t rest_head;         // staged picks: the next of them (as `more`)
   uint32_t pad0[10];
   unsigned long long useful;  // sum of idx + 1
   unsigned long long sweep;   // sweep evaluations
@@ -73,7 +73,13 @@ struct alignas(64) Counters {
   unsigned long long inertia_entries;  // layer and sublayer element matrices formed by them
   unsigned long long inertia_pivots;   // 2x2 block pivots eliminated by them
   uint32_t hist[kBuckets];    // work-order histogram, then bucket offsets
+  // staged picks: further queue heads beside queue_head and rest_head, each in a
+  // cache line of its own (as many as the workspace's alignment leaves for free)
+  struct alignas(64) Heads {
+    uint32_t head[2];
+  } more[2];
 };
+static_assert(sizeof(Counters) == 1280, "a multiple of the workspace's alignment");
 
 // Shared sweep of one work item that idle workgroups may join (queue
 // positions below SweepArgs::n_coop).  The item's grid is cut into rounds of

@@ -11,22 +11,31 @@
 //       order.  Its candidate goes to out_idx.  Without the eliminations it
 //       needs few registers (FP32: eight wavefronts per SIMD).
 //   pick_kernel: eight lanes per wavelength, eight wavelengths of one model
-//       at a time.  Split: the FP64 points from four before the candidate to
-//       three after it; the first one with E != 0 whose predecessor has E = 0
-//       is the pick if sign(det K) changes there, since E = 0 proves that
-//       there is no earlier change (masw_inertia.hpp).  Then, and on the walk
-//       at once, the refinement by eight points a round (Refine8), whose
-//       first round has K's own signs at the pick's two grid points.
+//       at a time.  Split: FP64 points at the grid's start and from three
+//       before the candidate to three after it, seven neighbours.  Where the
+//       counts E at the start and at the first of the seven are equal there is
+//       no change up to that one (masw_inertia.hpp), and the first of the
+//       others where sign(det K) changes is the pick.  Then, and on the walk at
+//       once, the refinement by eight points a round (Refine8), whose first
+//       round has K's own signs at the pick's two grid points, and their counts.
 //   pick_rest_kernel: the others (no change found in FP32, a grid that starts
 //       below c_low, a candidate that the eight points do not settle, a pole in
 //       the step or several changes of E, a step at or above the half-space's S
-//       velocity, a change that the elimination does not confirm), by a whole wavefront each, as the one-launch sweep does them
-//       from the candidate on.
+//       velocity, a change that the elimination does not confirm), by a whole
+//       wavefront each, as the one-launch sweep does them from the candidate on;
+//       past a candidate that was none, from the last of the seven points on.
 // Between the launches out_idx holds the candidate, or kDeferredIdx with the
-// candidate (-1: none) in out_status.  Indices, statuses and roots are those
-// of the one-launch sweep: the same eliminations at the same points decide.
-// The 1.12 M wavelengths (19,001 velocities): 160 -> 151 ms, split 83 -> 69;
-// before the sweeps' sign function, 211 and 98.
+// candidate (-1: none) in out_status and, on the split path, in out_ct where to
+// go on after it (4 times the position plus the sign before it; 0: nowhere).
+// Indices, statuses and roots are those of the one-launch sweep: the same
+// eliminations at the same points decide.
+// The 1.12 M wavelengths (19,001 velocities): 160 -> 151 ms, split 83 -> 68;
+// before the sweeps' sign function, 211 and 98.  What one launch and three take
+// differs most on short grids: 124,000 wavelengths x 2,000 velocities 2.83 and
+// 2.00 ms (split 2.49 and 1.28), on models of strong contrast, a ninth of whose
+// first candidates are a mode and a pole in one grid step, 2.22 and 1.98 (2.12
+// and 1.90); 46,500 of the latter 0.87 and 0.97 on the split path, the others
+// 0.99 and 0.62.
 #define MASW_COEFF_POLICY 1
 #include "masw_inertia_kernel.hpp"
 #include "masw_sweep.hpp"
@@ -40,13 +49,46 @@ namespace {
 template <int MODE>
 constexpr int kSweepWaves = MODE == kModeSplit ? 7 : 6;
 
+// Work claimed one unit at a time from kQueues counters of their own cache
+// lines, unit kQueues i + x being the i-th of counter x, and the next counter's
+// when one has run out.  Claims of one counter serialise at 12 ns each, which was
+// all of the 1441 us of the FP32 sweep of 124,000 wavelengths to 278 velocities
+// on average: 509 us with three counters and two items a claim (557 and 605 us
+// with four and two items a claim of one counter).
+constexpr unsigned kQueues = 1 + sizeof(Counters::more) / sizeof(Counters::Heads);
+struct Claims {
+  unsigned x, tried;
+  // Unit of queue `which` (0: the sweep's items, 1: the last launch's list) of
+  // n units, or n when all are taken.
+  __device__ __forceinline__ unsigned next(Counters* c, int which, unsigned n) {
+    while (tried < kQueues) {
+      uint32_t* head = x == 0u ? (which ? &c->rest_head : &c->queue_head) : &c->more[x - 1u].head[which];
+      unsigned i = 0;
+      if ((threadIdx.x & 63) == 0) i = atomicAdd(head, 1u);
+      i = kQueues * unsigned(uniform(int(i))) + x;
+      if (i < n) return i;
+      ++tried;
+      x = x + 1u < kQueues ? x + 1u : 0u;
+    }
+    return n;
+  }
+};
+
+// Items a sweeping wavefront takes at a time after its first: two where there are
+// eight or more for each, one below.  46,500 wavelengths x 9,501 velocities, 6.5 a
+// wavefront, took 1.70 ms with one, 1.74 with two and 1.87 with four; items dealt
+// out without a claim made large batches 10 to 20% slower.
+constexpr unsigned kItemsForTwo = 8;
+
 template <int MODE>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kSweepWaves<MODE>)))
 void first_change_kernel(SweepArgs a) {
   const int lane = threadIdx.x;
   WorkCount wc;
   stamp_start(a.tstamp, 1);
-  for (unsigned it = blockIdx.x;;) {
+  Claims claims{blockIdx.x % kQueues, 0u};
+  const unsigned claim = unsigned(a.n_items) >= kItemsForTwo * gridDim.x ? 2u : 1u;
+  for (unsigned it = blockIdx.x, left = 0;;) {
     if (it >= unsigned(a.n_items)) break;
     int g;
     const ItemRef r = item_ref(a, int(it), &g);
@@ -82,11 +124,16 @@ void first_change_kernel(SweepArgs a) {
       } else if (lane == 0) {
         *o.idx = found < 0 ? kDeferredIdx : found;
         *o.status = found;
+        if (found < 0) *o.ct = 0.0;
       }
     }
-    unsigned q = 0;
-    if (lane == 0) q = atomicAdd(&a.counters->queue_head, 1u);
-    it = gridDim.x + unsigned(uniform(int(q)));
+    if (left > 0u) {
+      ++it;
+      --left;
+    } else {
+      it = gridDim.x + claim * claims.next(a.counters, 0, (unsigned(a.n_items) - gridDim.x + claim - 1u) / claim);
+      left = claim - 1u;
+    }
   }
   __builtin_amdgcn_s_setprio(0);
   flush_counts(a.counters, a.wg_counts, wc);
@@ -122,35 +169,44 @@ __device__ __forceinline__ void run_picks(const SweepArgs& a, int begin, int end
       live = true;
       check = MODE == kModeSplit;
       if (check) {
-        first = max(0, min(at - 4, n_c - 8));
+        first = max(0, min(at - 3, n_c - 7));
       } else {
         r.init(c64[at - 1], c64[at], a.refine_rel);
       }
     }
     if (__ballot(live) == 0ull) break;
-    const double c = check ? c64[min(first + sub, n_c - 1)] : r.point(sub);
-    const Point v = eval_point<true>(c, k, L, N, live && (check || (r.stage == 0 && r.round == 0)));
+    const bool opens = r.stage == 0 && r.round == 0;  // the refinement's first round
+    const double c = check ? c64[sub == 0 ? 0 : min(first + sub - 1, n_c - 1)] : r.point(sub);
+    const Point v = eval_point<true>(c, k, L, N, live && (check || (opens && (sub == 0 || sub == 7))));
     const int sg_prev = previous_lane(v.sg);
-    const unsigned above = in_group(!v.zero), pole = in_group(v.pole);
     const unsigned changes = in_group(sub > 0 && v.sg != sg_prev), nan = in_group(v.sg == kNaNSign);
     wc.check += __popcll(__ballot(live && check));
     wc.refine += __popcll(__ballot(live && !check));
     bool rest = false, done = false;
+    int resume = 0;
     if (live && check) {
-      const int f = above ? __ffs(int(above)) - 1 : 0;  // first point with E != 0
+      // equal counts at the grid's start and at the first of the seven points:
+      // no change up to there; the seven are neighbours
+      const int E_0 = from_lane<false>(v.E, base), E_1 = from_lane<false>(v.E, base + 1);
+      const unsigned later = changes & 0xfcu;
+      const int f = later ? __ffs(int(later)) - 1 : 0;
       const double c_lo = from_lane<false>(c, base + max(f - 1, 0)), c_hi = from_lane<false>(c, base + f);
-      at = f > 0 ? first + f : at;
-      rest = f == 0 || !(changes >> f & 1u) || (nan >> f & 1u);
+      const bool certain = E_0 == E_1 && E_0 != inertia::kEvent && nan == 0u;
+      rest = !certain || f == 0;
+      // (no change among the seven: the last launch goes on from the last one)
+      resume = certain && f == 0 && first + 7 < n_c ? (first + 7) * 4 + from_lane<false>(v.sg, base + 7) : 0;
+      at = rest ? at : first + f - 1;
       r.init(c_lo, c_hi, a.refine_rel);
       check = false;
     } else if (live) {
-      // one change of E over the step, and no pole: a single root
-      const int s_lo = from_lane<false>(v.sg, base), s_hi = from_lane<false>(v.sg, base + 7);
-      const int E_lo = from_lane<false>(v.E, base), E_hi = from_lane<false>(v.E, base + 7);
-      if (r.stage == 0 && r.round == 0 &&
-          (pole != 0u || nan != 0u || s_lo == s_hi || E_hi == inertia::kEvent || E_hi != E_lo + 1))
-        rest = true;
-      else
+      // E one larger at the step's upper end, and no pole in it: a single root
+      if (opens) {
+        const int s_lo = from_lane<false>(v.sg, base), s_hi = from_lane<false>(v.sg, base + 7);
+        const int E_lo = from_lane<false>(v.E, base), E_hi = from_lane<false>(v.E, base + 7);
+        const int P_lo = from_lane<false>(v.P, base), P_hi = from_lane<false>(v.P, base + 7);
+        rest = nan != 0u || s_lo == s_hi || E_hi == inertia::kEvent || E_hi != E_lo + 1 || P_hi != P_lo;
+      }
+      if (!rest)
         done = r.update(c, v.sg, v.m, v.e, base) || !a.refine;
     }
     if (rest || done) {
@@ -158,6 +214,7 @@ __device__ __forceinline__ void run_picks(const SweepArgs& a, int begin, int end
       if (sub == 0) {
         *o.idx = rest ? kDeferredIdx : at;
         *o.status = rest ? at : MASW_STATUS_FOUND;
+        if (MODE == kModeSplit && rest) *o.ct = double(resume);
         if (done) {
           *o.ct = c64[at];
           if (o.cref) *o.cref = o.refine ? 0.5 * (r.lo + r.hi) : __builtin_nan("");
@@ -212,16 +269,25 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void pi
   __shared__ SweepShared<1> sh;
   const unsigned n = a.counters->deferred;
   WorkCount wc;
+  Claims claims{blockIdx.x % kQueues, 0u};
   while (n != 0u) {
-    unsigned i = 0;
-    if (threadIdx.x == 0) i = atomicAdd(&a.counters->rest_head, 1u);
-    i = unsigned(uniform(int(i)));
+    const unsigned i = claims.next(a.counters, 1, n);
     if (i >= n) break;
     const int g = uniform(a.order[i]);
     const ItemRef r = item_of(a, g);
     const ItemOut o = item_out(a, g);
     ItemState st = item_state_init();
-    run_item<MODE, 1, kFromRest>(r, st, 0x7fffffff, sh, wc, o, kNoCoop, a.counters, uniform(*o.status));
+    int swept = uniform(*o.status);
+    if constexpr (MODE == kModeSplit) {
+      const int resume = uniform(int(*o.ct));
+      if (resume != 0) {  // past the candidate, with the determinant's sign at seg_start - 1
+        st.seg_start = (resume + 1) >> 2;
+        st.seg_carry = resume - 4 * st.seg_start;
+        st.start = st.seg_start - 1;
+        swept = kNotSwept;
+      }
+    }
+    run_item<MODE, 1, kFromRest>(r, st, 0x7fffffff, sh, wc, o, kNoCoop, a.counters, swept);
   }
   flush_counts(a.counters, a.wg_counts, wc);
   if (n != 0u) stamp_end(a.tstamp);

@@ -460,7 +460,7 @@ __device__ __forceinline__ bool walk_by_k(const ItemRef& r, ItemState& st, int b
 // FROM: the kernel that runs the item.
 //   kFromSweep: a batch launch.
 //   kFromRest:  the first sweep has been made, by another launch; its candidate
-//               is `swept` (-1: none).
+//               is `swept` (-1: none; kNotSwept: begun, and to go on from `st`).
 //   kFromFused: the sweep in minors does not look at c_low, which would put a
 //               wait in front of its first round (0.35 us of the 11 us of 30
 //               wavelengths x 801 velocities); wavefront 1 does while the first
@@ -468,6 +468,7 @@ __device__ __forceinline__ bool walk_by_k(const ItemRef& r, ItemState& st, int b
 //   kFromTick:  resumed in later ticks; a walk by the elimination begins in the
 //               next one.
 enum { kFromSweep, kFromRest, kFromFused, kFromTick };
+constexpr int kNotSwept = -2;
 template <int MODE, int G, int FROM>
 __device__ __forceinline__ bool run_item(const ItemRef& r, ItemState& st, int budget, SweepShared<G>& sh, WorkCount& wc,
                          const ItemOut& o, const CoopRef& co, Counters* cnt, int swept = 0) {
@@ -490,7 +491,7 @@ __device__ __forceinline__ bool run_item(const ItemRef& r, ItemState& st, int bu
     const float k32 = float(r.k64);
     const int n32 = r.n_real;
     int seg_start = st.seg_start, seg_carry = st.seg_carry;
-    bool shared = SWEPT || co.ci != nullptr;  // the first FP32 pass is a shared sweep, or made
+    bool shared = SWEPT ? swept != kNotSwept : co.ci != nullptr;  // the first FP32 pass is made, or a shared sweep
     for (;;) {
       // FP32 sweep for a candidate, from `start` (inside the segment that
       // began at seg_start, whose predecessor's FP64 sign is seg_carry).
