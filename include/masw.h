@@ -300,11 +300,14 @@ int masw_dispersion_batch(masw_ctx *ctx, const double *c_test, int32_t n_c,
  * misfit[m] = mean over its wavelengths i of |C_t,i - C_e,i| / C_e,i, as
  * masw_misfit computes it (bit for bit), in the same persistent launch: the
  * workgroup that finishes a model's last wavelength reduces the model's
- * misfit.  C_e: [total wavelengths], laid out as batch->lambda, finite and
+ * misfit.  Batches large enough that the sweep and the picks are launches of
+ * their own have a further one for the misfits; their device time
+ * (masw_timing) contains it.  C_e: [total wavelengths], laid out as batch->lambda, finite and
  * > 0 (checked on the host for host pointers); misfit: [n_models] (NaN for a
  * model without wavelengths, or with a wavelength without a pick).  With
- * MASW_SEARCH_INERTIA the misfit is a second launch after the search.  Same
- * rules as masw_dispersion_batch otherwise. */
+ * MASW_SEARCH_INERTIA the misfit is a second launch after the search, which
+ * the device time does not contain.  Same rules as masw_dispersion_batch
+ * otherwise. */
 int masw_dispersion_batch_misfit(masw_ctx *ctx, const double *c_test, int32_t n_c,
                                  const masw_batch *batch, masw_precision prec,
                                  uint32_t flags, void *stream, const masw_outputs *out,

@@ -38,8 +38,10 @@ hipError_t launch_prep(const PrepArgs& a, const CoopInitArgs& ci, int single_N, 
 hipError_t launch_sign_map(bool fp32, const SignMapArgs& a, hipStream_t s);
 hipError_t launch_admit(const AdmitList* list_dev, int n, int max_raw, int32_t* slot_remaining, hipStream_t s);
 hipError_t launch_tick(int G, int blocks, hipStream_t s, const TickArgs& a);
+// Algorithm 2 as a launch of its own; tstamp: the timing slot of a call whose
+// device time it ends (else null).
 hipError_t launch_misfit(int n_models, const int32_t* lambda_off, const double* c_t, const double* c_e,
-                         double* out, hipStream_t s);
+                         double* out, unsigned long long* tstamp, hipStream_t s);
 
 // Device arrays of a zero/pole classification (masw_classify.hip), laid out
 // as masw_batch plus the bracket indices and the two outputs.

@@ -597,7 +597,8 @@ void tick_kernel(TickArgs a) {
 // sums a strided subset in order, then a fixed-order tree in LDS.
 __global__ __launch_bounds__(256) void misfit_kernel(int n_models, const int32_t* __restrict__ lambda_off,
                                                      const double* __restrict__ c_t,
-                                                     const double* __restrict__ c_e, double* __restrict__ out) {
+                                                     const double* __restrict__ c_e, double* __restrict__ out,
+                                                     unsigned long long* tstamp) {
   __shared__ double s[256];
   const int m = blockIdx.x;
   if (m >= n_models) return;
@@ -611,12 +612,13 @@ __global__ __launch_bounds__(256) void misfit_kernel(int n_models, const int32_t
     __syncthreads();
   }
   if (threadIdx.x == 0) out[m] = (hi > lo) ? s[0] / double(hi - lo) : __builtin_nan("");
+  stamp_end(tstamp);
 }
 
 hipError_t launch_misfit(int n_models, const int32_t* lambda_off, const double* c_t, const double* c_e,
-                         double* out, hipStream_t st) {
+                         double* out, unsigned long long* tstamp, hipStream_t st) {
   if (n_models <= 0) return hipSuccess;
-  hipLaunchKernelGGL(misfit_kernel, dim3(n_models), dim3(256), 0, st, n_models, lambda_off, c_t, c_e, out);
+  hipLaunchKernelGGL(misfit_kernel, dim3(n_models), dim3(256), 0, st, n_models, lambda_off, c_t, c_e, out, tstamp);
   return hipGetLastError();
 }
 

@@ -261,6 +261,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void p
     row[2] = wc.refine;
     row[3] = wc.useful;
   }
+  __syncthreads();  // the stamp is thread 0's: the end of all four wavefronts
   stamp_end(a.tstamp);
 }
 
@@ -290,7 +291,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void pi
     run_item<MODE, 1, kFromRest>(r, st, 0x7fffffff, sh, wc, o, kNoCoop, a.counters, swept);
   }
   flush_counts(a.counters, a.wg_counts, wc);
-  if (n != 0u) stamp_end(a.tstamp);
+  stamp_end(a.tstamp);
 }
 
 // Each launch's rows of work counts follow those of the one before; *rows is
