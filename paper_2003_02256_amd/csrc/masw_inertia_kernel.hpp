@@ -193,6 +193,15 @@ __device__ __forceinline__ void run_groups(const SweepArgs& a, int begin, int en
   r.init(0.0, 0.0, 0.0);
   bool fresh = true, live = g < g_end;
   while (__ballot(live) != 0ull) {
+    if constexpr (U) {  // one wavelength: branches and addresses by scalar values
+      stage = __builtin_amdgcn_readfirstlane(stage);
+      lo = __builtin_amdgcn_readfirstlane(lo);
+      hi = __builtin_amdgcn_readfirstlane(hi);
+      at = __builtin_amdgcn_readfirstlane(at);
+      g = __builtin_amdgcn_readfirstlane(g);
+      fresh = __ballot(fresh) != 0ull;
+      live = true;
+    }
     if (fresh && live) {
       k = a.lam_k[g];
       stage = kFirst;
