@@ -89,7 +89,10 @@ enum {
  *                  grid at or above the half-space's S velocity is walked in
  *                  FP64, and the refinement is FP64.  So idx is Algorithm 1's
  *                  FP64 pick, as with MASW_PREC_FP64, outside the FP64 noise
- *                  band.  A curve or batch call whose grid has fewer than
+ *                  band.  Models on which FP32 signs are rounding noise (a
+ *                  stiff layer over a much softer one, on a grid that starts
+ *                  far below the former's S velocity) are walked in FP64.
+ *                  A curve or batch call whose grid has fewer than
  *                  MASW_SPLIT_MIN_GRID points runs as MASW_PREC_FP64 (two
  *                  rounds of a small launch's sweep cover such a grid, so
  *                  the FP32 sweep saves none of them, and its FP64 re-check

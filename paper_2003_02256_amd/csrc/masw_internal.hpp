@@ -22,6 +22,8 @@ namespace masw {
 constexpr int kNoSign = 0x7f;        // "no predecessor" marker in the sign scan
 constexpr int kNaNSign = 2;          // sign code of a NaN determinant
 constexpr int kBuckets = 256;        // work-order buckets
+constexpr float kLowest32 = 1.0f / 12.0f;  // FP32 sweeps: lowest start of the grid (masw_secular.hpp)
+constexpr float kInversion = 2.0f;          // and the contrast of the layers concerned
 constexpr double kRefineRel = 1e-9;  // default refinement bracket width / c_hi
 constexpr int kPrepThreads = 256;    // threads per staging block
 constexpr int kLamBlock = 1024;      // wavelengths sorted by one staging block
@@ -51,7 +53,8 @@ struct alignas(32) ModelDesc {
   int32_t n_lam;       // wavelengths
   int32_t valid;       // 1 if the model and its grid passed validation
   int32_t n_real;      // grid points c with c^2 / beta_hs^2 < 1 (K real, inertia counts exist): the
-                       // leading part of the grid, where the split path sweeps in FP32
+                       // leading part of the grid, where the split path sweeps in FP32; 0 for a
+                       // model whose signs FP32 does not give (masw_secular.hpp)
 };
 
 // Counters written by the kernels (one block in the arena, zeroed per call).

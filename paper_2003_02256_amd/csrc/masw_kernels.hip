@@ -54,11 +54,18 @@ __device__ void build_model(const PrepArgs& a, int m, int single_N, int single_W
   // whose outcomes form a prefix, and keeps the gap after the last point
   // below; two or three dependent loads for the usual grids instead of a
   // binary search's ten to fifteen.
+  // None of them where FP32 signs are rounding noise (masw_secular.hpp).
   int n_real = 0;
+  float b_max = 0.0f, b_inv = 0.0f;  // the largest beta, and the largest over a much slower layer
   if (ok) {
+    for (int j0 = 0; j0 <= N; j0 += 64) {
+      const bool is = j0 + lane <= N;
+      const float inv = secular::inversion(is ? float(a.beta[rec0 + j0 + lane]) : 0.0f, is, &b_max);
+      b_inv = __builtin_fmaxf(b_inv, inv);
+    }
     const double be = a.beta[rec0 + N];
     const double ib2 = 1.0 / (be * be);
-    int lo = 0, hi = a.n_c;  // n_real in [lo, hi]
+    int lo = 0, hi = a.c_in[0] < b_inv * kLowest32 ? 0 : a.n_c;  // n_real in [lo, hi]
     while (lo < hi) {
       const int step = (hi - lo + 63) / 64;
       const int i = lo + lane * step;
@@ -97,15 +104,12 @@ __device__ void build_model(const PrepArgs& a, int m, int single_N, int single_W
   if (!ok) return;
   const double mu_ref = a.rho[rec0 + N] * a.beta[rec0 + N] * a.beta[rec0 + N];
   double z0 = 0.0;  // depth of the top of this 64-layer chunk
-  float b_max = 0.0f;  // the largest beta so far (in FP32: it only places a limit)
   for (int j0 = 0; j0 <= N; j0 += 64) {
     const int j = j0 + lane;
     // depth of each layer's bottom: inclusive prefix sum over the chunk
     double z = (j < N) ? a.h[lo + j] : 0.0;
-    b_max = __builtin_fmaxf(b_max, j <= N ? float(a.beta[rec0 + j]) : 0.0f);
     for (int off = 1; off < 64; off <<= 1) {
       const double up = __shfl_up(z, off, 64);
-      b_max = __builtin_fmaxf(b_max, __shfl_xor(b_max, off, 64));
       if (lane >= off) z += up;
     }
     z += z0;

@@ -602,7 +602,14 @@ int masw_submit(masw_ctx* ctx, const double* c_test, int32_t n_c, const double* 
     // device's inertia-count test (the grid rises, checked above)
     const double be = model->beta[N];
     const double ib2 = 1.0 / (be * be);
-    int lo = 0, hi = n_c;
+    // (none where FP32 signs are rounding noise, as build_model has it)
+    float b_max = 0.0f, b_inv = 0.0f;
+    for (int j = 0; j <= N; ++j) {
+      const float b = float(model->beta[j]);
+      if (b_max > kInversion * b) b_inv = b_max;
+      b_max = std::max(b_max, b);
+    }
+    int lo = 0, hi = c_test[0] < b_inv * kLowest32 ? 0 : n_c;
     while (lo < hi) {
       const int mid = (lo + hi) >> 1;
       const double c = c_test[mid];

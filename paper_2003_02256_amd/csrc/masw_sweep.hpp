@@ -483,7 +483,9 @@ __device__ __forceinline__ bool run_item(const ItemRef& r, ItemState& st, int bu
   int start = st.start, carry = st.carry, rounds = 0;
   bool fp64 = (MODE == kModeFP64) || st.fp64;
 
-  if (!fp64 && r.n_real <= 0) {  // the whole grid at or above the half-space's S velocity
+  // the whole grid at or above the half-space's S velocity, or signs that FP32
+  // does not give
+  if (!fp64 && r.n_real <= 0) {
     fp64 = true;
     st.fp64 = 1;
   }
@@ -875,8 +877,10 @@ __device__ void model_finished(const SweepArgs& a, int m, SweepShared<G>& sh, do
 // (model_finished), an instantiation of its own so that the plain sweeps
 // keep their register allocation; it and the plain FP64 sweeps are held to
 // 128 VGPRs (4 wavefronts per SIMD), which they fit without spilling.
-// The plain split sweeps are held to 96 VGPRs (5 wavefronts per SIMD), which
-// their FP32 loop fits without spilling.
+// The plain split sweeps are held to 96 VGPRs (5 wavefronts per SIMD): their FP32
+// loop fits, and 2 to 8 of the eliminations' registers spill.  With four
+// wavefronts none do, and 1000 wavelengths x 115,001 velocities (G = 8) take
+// 753 us instead of 705, 15,500 x 9,501 (G = 1) 1015 instead of 985.
 template <int MODE, int G, bool MISFIT>
 __global__ __launch_bounds__(64 * G) __attribute__((amdgpu_waves_per_eu((MODE == kModeSplit && !MISFIT) ? 5 : 4)))
 void sweep_kernel(SweepArgs a) {
@@ -1005,8 +1009,16 @@ __global__ __launch_bounds__(64 * kFusedG) void fused_sweep_kernel(SweepArgs a) 
   if constexpr (MODE == kModeSplit) {
     for (int o = 32; o > 0; o >>= 1) below += __shfl_xor(below, o, 64);
     if ((tid & 63) == 0 && below) atomicAdd(&s_below, below);
+    if (tid < 64 && !bad) {  // build_model's test of the layers
+      static_assert(kFusedMaxLayers <= 64, "the first 64 records, and the half-space's");
+      const auto beta_of = [&](int j) { return __builtin_amdgcn_rsqf(L32[j].ib2); };
+      float top = 0.0f;
+      float inv = secular::inversion(tid <= N ? beta_of(tid) : 0.0f, tid <= N, &top);
+      if (N == 64 && top > kInversion * beta_of(64)) inv = top;
+      if (a.f_c[0] < inv * kLowest32 && tid == 0) atomicAdd(&s_below, -(1 << 30));
+    }
     __syncthreads();
-    n_real = s_below;
+    n_real = max(s_below, 0);
   }
   const bool ok = !bad && (lam > 0.0) && (lam < __builtin_inf());
   ItemRef r;
