@@ -29,7 +29,8 @@ hipError_t launch_sweep(int mode, int G, int blocks, hipStream_t s, const SweepA
 // A fused small launch (SweepArgs::fused): `blocks` workgroups of kFusedG
 // wavefronts, one wavelength each.
 hipError_t launch_fused(int mode, int blocks, hipStream_t s, const SweepArgs& a);
-// The same with one wavefront per item, in three launches (masw_picks.hip).
+// A sweep with one wavefront per item, in three launches (masw_picks.hip), and a
+// fourth for the misfits if asked for.
 // *rows: the rows of a.wg_counts they write.
 hipError_t launch_staged_picks(int mode, int cus, hipStream_t s, const SweepArgs& a, int* blocks_out, int* rows);
 // The inertia-count search (masw_inertia.hip), 64, 32 or 8 lanes per wavelength.
@@ -38,10 +39,10 @@ hipError_t launch_prep(const PrepArgs& a, const CoopInitArgs& ci, int single_N, 
 hipError_t launch_sign_map(bool fp32, const SignMapArgs& a, hipStream_t s);
 hipError_t launch_admit(const AdmitList* list_dev, int n, int max_raw, int32_t* slot_remaining, hipStream_t s);
 hipError_t launch_tick(int G, int blocks, hipStream_t s, const TickArgs& a);
-// Algorithm 2 as a launch of its own; tstamp: the timing slot of a call whose
-// device time it ends (else null).
 hipError_t launch_misfit(int n_models, const int32_t* lambda_off, const double* c_t, const double* c_e,
-                         double* out, unsigned long long* tstamp, hipStream_t s);
+                         double* out, hipStream_t s);
+// The same for a call whose device time it ends (SweepArgs::misfit, tstamp).
+hipError_t launch_staged_misfit(const SweepArgs& a, hipStream_t s);
 
 // Device arrays of a zero/pole classification (masw_classify.hip), laid out
 // as masw_batch plus the bracket indices and the two outputs.

@@ -620,9 +620,16 @@ __global__ __launch_bounds__(256) void misfit_kernel(int n_models, const int32_t
 }
 
 hipError_t launch_misfit(int n_models, const int32_t* lambda_off, const double* c_t, const double* c_e,
-                         double* out, unsigned long long* tstamp, hipStream_t st) {
+                         double* out, hipStream_t st) {
   if (n_models <= 0) return hipSuccess;
-  hipLaunchKernelGGL(misfit_kernel, dim3(n_models), dim3(256), 0, st, n_models, lambda_off, c_t, c_e, out, tstamp);
+  hipLaunchKernelGGL(misfit_kernel, dim3(n_models), dim3(256), 0, st, n_models, lambda_off, c_t, c_e, out,
+                     static_cast<unsigned long long*>(nullptr));
+  return hipGetLastError();
+}
+
+hipError_t launch_staged_misfit(const SweepArgs& a, hipStream_t st) {
+  hipLaunchKernelGGL(misfit_kernel, dim3(a.n_models), dim3(256), 0, st, a.n_models, a.lambda_off, a.out_ct, a.c_e,
+                     a.misfit, a.tstamp);
   return hipGetLastError();
 }
 

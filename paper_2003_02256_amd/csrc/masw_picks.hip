@@ -312,7 +312,8 @@ hipError_t launch(int cus, hipStream_t s, const SweepArgs& a, int* blocks_out, i
   hipLaunchKernelGGL(pick_kernel<MODE>, dim3(picking), dim3(256), 0, s, b, chunk);
   b.wg_counts += size_t(picking) * 4 * kWgCounts;
   hipLaunchKernelGGL(pick_rest_kernel<MODE>, dim3(rest), dim3(64), 0, s, b);
-  return hipGetLastError();
+  const hipError_t e = hipGetLastError();
+  return e != hipSuccess || !a.misfit ? e : launch_staged_misfit(a, s);
 }
 
 }  // namespace

@@ -465,7 +465,7 @@ int run_curves(masw_ctx* ctx, const Inputs& in, masw_precision prec, uint32_t fl
   sw.refine = (flags & MASW_NO_REFINE) ? 0 : 1;
   sw.refine_rel = ctx->refine_rel;
   sw.counters = p.counters;
-  if (in.misfit && !inertia && !staged) {  // (a separate misfit launch below)
+  if (in.misfit && !inertia) {
     sw.c_e = c_e_dev;
     sw.misfit = misfit_dev;
     sw.model_left = p.model_left;
@@ -479,13 +479,11 @@ int run_curves(masw_ctx* ctx, const Inputs& in, masw_precision prec, uint32_t fl
     MASW_HIP(inertia  ? launch_inertia(sw, ctx->cus, s, &blocks)
              : staged ? launch_staged_picks(mode, ctx->cus, s, sw, &blocks, &count_rows)
                       : launch_sweep(mode, G, blocks, s, sw));
-  // the misfits' own launch belongs to a walk's device time, as where the sweep
-  // reduces them, and not to that of an inertia search
-  if (in.misfit && staged)
-    MASW_HIP(launch_misfit(in.n_models, p.lambda_off, sw.out_ct, c_e_dev, misfit_dev, sw.tstamp, s));
+  // (the misfits of a walk belong to its device time, also as a launch of their
+  // own; those of an inertia search do not)
   if (T && T->events) MASW_HIP(hipEventRecord(T->ev[2], s));
   if (in.misfit && inertia)
-    MASW_HIP(launch_misfit(in.n_models, p.lambda_off, sw.out_ct, c_e_dev, misfit_dev, nullptr, s));
+    MASW_HIP(launch_misfit(in.n_models, p.lambda_off, sw.out_ct, c_e_dev, misfit_dev, s));
   // optional diagnostic after the timed sweep: the FP64 noise band of each
   // pick's bracket
   if ((flags & MASW_CHECK_NOISE) && in.n_lam > 0)
@@ -934,7 +932,7 @@ int masw_misfit(masw_ctx* ctx, int32_t n_models, const int32_t* lambda_off, cons
   hipStream_t s = static_cast<hipStream_t>(stream);  // NULL: the default stream
   if (dev) {
     // reads and writes only caller memory: no arena claim
-    MASW_HIP(launch_misfit(n_models, lambda_off, C_t, C_e, misfit, nullptr, s));
+    MASW_HIP(launch_misfit(n_models, lambda_off, C_t, C_e, misfit, s));
     ctx->last_stream = s;
     ctx->last_valid = true;
     return MASW_OK;
@@ -953,7 +951,7 @@ int masw_misfit(masw_ctx* ctx, int32_t n_models, const int32_t* lambda_off, cons
     MASW_HIP(hipMemcpyAsync(d_ct, C_t, sizeof(double) * W, hipMemcpyHostToDevice, s));
     MASW_HIP(hipMemcpyAsync(d_ce, C_e, sizeof(double) * W, hipMemcpyHostToDevice, s));
   }
-  MASW_HIP(launch_misfit(n_models, d_off, d_ct, d_ce, d_out, nullptr, s));
+  MASW_HIP(launch_misfit(n_models, d_off, d_ct, d_ce, d_out, s));
   MASW_HIP(hipMemcpyAsync(misfit, d_out, sizeof(double) * n_models, hipMemcpyDeviceToHost, s));
   MASW_HIP(hipStreamSynchronize(s));
   ctx->last_stream = s;
