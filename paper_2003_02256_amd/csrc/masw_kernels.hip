@@ -597,25 +597,27 @@ void tick_kernel(TickArgs a) {
 }
 
 // -------------------------------------------------------------- misfit --
-// Algorithm 2 per model: one workgroup of 256 threads per model; each thread
-// sums a strided subset in order, then a fixed-order tree in LDS.
+// Algorithm 2 per model: a workgroup of 256 threads takes models blockIdx.x,
+// blockIdx.x + gridDim.x, ...; each thread sums a strided subset in order, then
+// a fixed-order tree in LDS.
 __global__ __launch_bounds__(256) void misfit_kernel(int n_models, const int32_t* __restrict__ lambda_off,
                                                      const double* __restrict__ c_t,
                                                      const double* __restrict__ c_e, double* __restrict__ out,
                                                      unsigned long long* tstamp) {
   __shared__ double s[256];
-  const int m = blockIdx.x;
-  if (m >= n_models) return;
-  const int lo = lambda_off[m], hi = lambda_off[m + 1];
-  double acc = 0.0;
-  for (int i = lo + threadIdx.x; i < hi; i += blockDim.x) acc += ::fabs(c_t[i] - c_e[i]) / c_e[i];
-  s[threadIdx.x] = acc;
-  __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if (threadIdx.x < w) s[threadIdx.x] += s[threadIdx.x + w];
+  for (int m = blockIdx.x; m < n_models; m += gridDim.x) {
+    const int lo = lambda_off[m], hi = lambda_off[m + 1];
+    double acc = 0.0;
+    for (int i = lo + threadIdx.x; i < hi; i += blockDim.x) acc += ::fabs(c_t[i] - c_e[i]) / c_e[i];
+    __syncthreads();  // s is the last model's until here
+    s[threadIdx.x] = acc;
     __syncthreads();
+    for (int w = 128; w > 0; w >>= 1) {
+      if (threadIdx.x < w) s[threadIdx.x] += s[threadIdx.x + w];
+      __syncthreads();
+    }
+    if (threadIdx.x == 0) out[m] = (hi > lo) ? s[0] / double(hi - lo) : __builtin_nan("");
   }
-  if (threadIdx.x == 0) out[m] = (hi > lo) ? s[0] / double(hi - lo) : __builtin_nan("");
   stamp_end(tstamp);
 }
 
@@ -628,8 +630,9 @@ hipError_t launch_misfit(int n_models, const int32_t* lambda_off, const double* 
 }
 
 hipError_t launch_staged_misfit(const SweepArgs& a, hipStream_t st) {
-  hipLaunchKernelGGL(misfit_kernel, dim3(a.n_models), dim3(256), 0, st, a.n_models, a.lambda_off, a.out_ct, a.c_e,
-                     a.misfit, a.tstamp);
+  // (each workgroup stamps its end, 12 ns one after the other)
+  hipLaunchKernelGGL(misfit_kernel, dim3(std::min(a.n_models, 1024)), dim3(256), 0, st, a.n_models, a.lambda_off,
+                     a.out_ct, a.c_e, a.misfit, a.tstamp);
   return hipGetLastError();
 }
 

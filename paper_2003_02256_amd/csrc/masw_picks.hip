@@ -271,9 +271,11 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void pi
   const unsigned n = a.counters->deferred;
   WorkCount wc;
   Claims claims{blockIdx.x % kQueues, 0u};
+  bool took = blockIdx.x == 0;
   while (n != 0u) {
     const unsigned i = claims.next(a.counters, 1, n);
     if (i >= n) break;
+    took = true;
     const int g = uniform(a.order[i]);
     const ItemRef r = item_of(a, g);
     const ItemOut o = item_out(a, g);
@@ -291,7 +293,9 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void pi
     run_item<MODE, 1, kFromRest>(r, st, 0x7fffffff, sh, wc, o, kNoCoop, a.counters, swept);
   }
   flush_counts(a.counters, a.wg_counts, wc);
-  stamp_end(a.tstamp);
+  // (4096 maxima on one word would take 45 us: of the workgroups without an
+  // item, only the first stamps)
+  if (took) stamp_end(a.tstamp);
 }
 
 // Each launch's rows of work counts follow those of the one before; *rows is
