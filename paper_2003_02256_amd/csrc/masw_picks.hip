@@ -74,11 +74,15 @@ struct Claims {
   }
 };
 
-// Items a sweeping wavefront takes at a time after its first: two where there are
-// eight or more for each, one below.  46,500 wavelengths x 9,501 velocities, 6.5 a
-// wavefront, took 1.70 ms with one, 1.74 with two and 1.87 with four; items dealt
-// out without a claim made large batches 10 to 20% slower.
+// Items a sweeping wavefront takes at a time after its first: two in FP32 on
+// grids of up to kShortGrid points with eight items or more for each wavefront,
+// where the claims can bound the sweep: 120,000 wavelengths x 2,000 velocities
+// 973 us with one, 827 with two.  Else one, whose work ends more evenly: FP32,
+// 110,000 x 9,501, 3.83 ms against 3.91; FP64, twice as long an item, 54,000 x
+// 8,105 3.66 against 3.83.  (46,500 x 9,501 FP32 1.70 with one, 1.87 with four;
+// items dealt out without a claim made large batches 10 to 20% slower.)
 constexpr unsigned kItemsForTwo = 8;
+constexpr int kShortGrid = 4096;
 
 template <int MODE>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kSweepWaves<MODE>)))
@@ -87,7 +91,9 @@ void first_change_kernel(SweepArgs a) {
   WorkCount wc;
   stamp_start(a.tstamp, 1);
   Claims claims{blockIdx.x % kQueues, 0u};
-  const unsigned claim = unsigned(a.n_items) >= kItemsForTwo * gridDim.x ? 2u : 1u;
+  const bool two = MODE == kModeSplit && unsigned(a.n_items) >= kItemsForTwo * gridDim.x &&
+                   uniform(a.models[0].n_c) <= kShortGrid;
+  const unsigned claim = two ? 2u : 1u;
   for (unsigned it = blockIdx.x, left = 0;;) {
     if (it >= unsigned(a.n_items)) break;
     int g;
