@@ -34,16 +34,25 @@ __device__ void build_model(const PrepArgs& a, int m, int single_N, int single_W
   const int N = hi - lo;
   const int rec0 = lo + m;  // records and alpha/beta/rho entries of model m
   bool ok = (N >= 0) && (N <= MASW_MAX_LAYERS);
+  double c0 = 0.0;
+  float b_max = 0.0f, b_inv = 0.0f;  // the largest beta, and the largest over a much slower layer
   if (ok) {
+    c0 = a.c_in[0];
     bool lok = true;
-    for (int j = lane; j <= N; j += 64) {
-      const double al = a.alpha[rec0 + j], be = a.beta[rec0 + j], rh = a.rho[rec0 + j];
-      const bool finite = (al < __builtin_inf()) && (rh < __builtin_inf());
-      lok = lok && finite && (be > 0.0) && (al > be) && (rh > 0.0);
-      if (j < N) {
-        const double h = a.h[lo + j];
-        lok = lok && (h > 0.0) && (h < __builtin_inf());
+    for (int j0 = 0; j0 <= N; j0 += 64) {
+      const int j = j0 + lane;
+      double be = 0.0;
+      if (j <= N) {
+        be = a.beta[rec0 + j];
+        const double al = a.alpha[rec0 + j], rh = a.rho[rec0 + j];
+        const bool finite = (al < __builtin_inf()) && (rh < __builtin_inf());
+        lok = lok && finite && (be > 0.0) && (al > be) && (rh > 0.0);
+        if (j < N) {
+          const double h = a.h[lo + j];
+          lok = lok && (h > 0.0) && (h < __builtin_inf());
+        }
       }
+      b_inv = __builtin_fmaxf(b_inv, secular::inversion(float(be), j <= N, &b_max));
     }
     ok = __ballot(!lok) == 0ull;
   }
@@ -56,16 +65,10 @@ __device__ void build_model(const PrepArgs& a, int m, int single_N, int single_W
   // binary search's ten to fifteen.
   // None of them where FP32 signs are rounding noise (masw_secular.hpp).
   int n_real = 0;
-  float b_max = 0.0f, b_inv = 0.0f;  // the largest beta, and the largest over a much slower layer
   if (ok) {
-    for (int j0 = 0; j0 <= N; j0 += 64) {
-      const bool is = j0 + lane <= N;
-      const float inv = secular::inversion(is ? float(a.beta[rec0 + j0 + lane]) : 0.0f, is, &b_max);
-      b_inv = __builtin_fmaxf(b_inv, inv);
-    }
     const double be = a.beta[rec0 + N];
     const double ib2 = 1.0 / (be * be);
-    int lo = 0, hi = a.c_in[0] < b_inv * kLowest32 ? 0 : a.n_c;  // n_real in [lo, hi]
+    int lo = 0, hi = c0 < b_inv * kLowest32 ? 0 : a.n_c;  // n_real in [lo, hi]
     while (lo < hi) {
       const int step = (hi - lo + 63) / 64;
       const int i = lo + lane * step;
