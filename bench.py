@@ -8,7 +8,7 @@ the results in HBM.  Inputs are resident in HBM before timing starts.
 Default workload: the batch of 4096 seeded models of uneven sizes (N 3-30,
 50-500 wavelengths log-spaced 1-80 m each, about 1.1 M wavelengths; c 50-1000
 m/s at 0.05 m/s, 19,001 values; about 15% with a low-velocity layer), one
-persistent launch per job.  Headline: the plain FP64 path.  The split path
+call per job.  Headline: the plain FP64 path.  The split path
 (FP32 sweep + FP64 re-check and inertia-count certificate + FP64 refinement)
 and the FP64 inertia-count search are timed on the same inputs and reported
 beside it.  Legs of the default run:
@@ -86,7 +86,8 @@ def classify_flops(evals: int, layers: int, steps: int) -> float:
     return 61.0 * evals + 238.0 * layers + 95.0 * steps
 
 
-# HBM bytes per launch of the dominant kernel, from rocprofv3 FETCH_SIZE and
+# HBM bytes per launch of the dominant kernel (of all three, where the picks are
+# launches of their own), from rocprofv3 FETCH_SIZE and
 # WRITE_SIZE runs each scaled by the same counter's reading for a plain copy of
 # known size (FETCH x 2.000, WRITE x 1.000); see profiles/.  Keyed by the hash
 # of the kernel sources the counters were taken on (KERNEL_SOURCES for the
@@ -94,24 +95,27 @@ def classify_flops(evals: int, layers: int, steps: int) -> float:
 # classification), the workload and the
 # launch, so a changed kernel reports null until it is measured again.
 MEASURED_TRAFFIC = {
-    ("4e502a09f3d5959a", "fine_scale_N20_1000lam_115001c", "sweep_kernel<FP64,G=4>"):
-        8170.61 * 1024 * 2.000 + 4899.36 * 1024 * 1.000,
-    ("4e502a09f3d5959a", "batch_4096models_19001c", "sweep_kernel<FP64,G=1>"):
-        267238.81 * 1024 * 2.000 + 147567.77 * 1024 * 1.000,
-    ("31a58e2a8353c3d3", "fine_scale_N20_1000lam_115001c", "inertia_lone_kernel"):
-        902.00 * 1024 * 2.000 + 50.80 * 1024 * 1.000,
-    ("31a58e2a8353c3d3", "batch_4096models_19001c", "inertia_kernel"):
-        55078.56 * 1024 * 2.000 + 1205151.92 * 1024 * 1.000,
-    ("ef681d38c885d05d", "classify_batch_4096models_19001c", "classify_kernel"):
-        14642.625 * 1024 * 2.000 + 21872.34 * 1024 * 1.000,
+    ("9112600bc7ec7186", "two_layer_30lam_801c", "fused_sweep_kernel<FP64>"):
+        178.07 * 1024 * 2.000 + 6.04 * 1024 * 1.000,
+    ("9112600bc7ec7186", "fine_scale_N20_1000lam_115001c", "sweep_kernel<FP64,G=4>"):
+        8536.2 * 1024 * 2.000 + 4948.4 * 1024 * 1.000,
+    ("9112600bc7ec7186", "batch_4096models_19001c", "first_change_kernel<FP64>, pick_kernel, pick_rest_kernel"):
+        (234180.0 + 17772.0 + 47.5) * 1024 * 2.000 + (91000.0 + 133350.0 + 640.6) * 1024 * 1.000,
+    ("1f7062f53ef8ebbb", "fine_scale_N20_1000lam_115001c", "inertia_lone_kernel"):
+        755.4 * 1024 * 2.000 + 50.8 * 1024 * 1.000,
+    ("1f7062f53ef8ebbb", "batch_4096models_19001c", "inertia_kernel"):
+        22590.0 * 1024 * 2.000 + 37331.0 * 1024 * 1.000,
+    ("25c051127b7e4d55", "classify_batch_4096models_19001c", "classify_kernel"):
+        9265.4 * 1024 * 2.000 + 14217.0 * 1024 * 1.000,
 }
 
 # (timed steps, warm-up steps) per workload when the command line gives none.
 DEFAULT_STEPS = {"fine_scale": (200, 50), "two_layer": (200, 50), "batch": (5, 1), "uniform": (20, 3),
                  "chains": (100, 3), "classify": (5, 2)}
 
-KERNEL_SOURCES = ["masw_internal.hpp", "masw_math.hpp", "masw_special.hpp", "masw_pick.hpp", "masw_sweep.hpp",
-                  "masw_kernels.hip", "masw_sweep_split.hip"]
+KERNEL_SOURCES = ["masw_internal.hpp", "masw_math.hpp", "masw_special.hpp", "masw_secular.hpp", "masw_pick.hpp",
+                  "masw_inertia.hpp", "masw_inertia_kernel.hpp", "masw_sweep.hpp", "masw_kernels.hip",
+                  "masw_sweep_split.hip", "masw_picks.hip"]
 CLASSIFY_SOURCES = ["masw_classify.hip"]
 INERTIA_SOURCES = ["masw_internal.hpp", "masw_math.hpp", "masw_special.hpp", "masw_pick.hpp", "masw_inertia.hpp",
                    "masw_inertia_kernel.hpp", "masw_inertia.hip", "masw_inertia_lone.hip"]
@@ -610,10 +614,9 @@ def inertia_leg(wl, r64, r_i, wall64, wall_i, sweep_i, st_i, n_lay, n_curves):
     flops = (inertia_flops(st_i["inertia_evals"], st_i["inertia_entries"], st_i["inertia_pivots"])
              + det_evals * flops_per_eval(nbar))
     achieved = flops / (sweep_i * 1e-3) / 1e12
-    # the library runs the variant for at most one wavefront per SIMD when the
-    # wavelengths, four per workgroup (one per SIMD), need no more workgroups
-    # than there are CUs
-    lone = st_i["workgroups"] <= st_i["cus"]
+    # the persistent grid of the variant for many wavelengths has four
+    # workgroups on each CU
+    lone = st_i["workgroups"] < 4 * st_i["cus"]
     kname = "inertia_lone_kernel" if lone else "inertia_kernel"
     return {
         "value": wl.n_lambda_total / wall_i, "unit": "wavelengths/s",
@@ -687,9 +690,10 @@ def measure_curves(M, torch, wl, steps: int, warmup: int, inertia: bool = True) 
     def sweep_name(st, mode: str) -> str:
         if st.get("fused_staging"):
             return f"fused_sweep_kernel<{mode}>"
+        # with picks launched apart from it the sweep keeps six or seven
+        # wavefronts (workgroups of one) on a SIMD, with them five at most
         simds = 4 * torch.cuda.get_device_properties(0).multi_processor_count
-        if (st["waves_per_item"] == 1 and not st["shared_items"]
-                and st["n_lambda"] > (32 if mode == "split" else 48) * simds):
+        if st["waves_per_item"] == 1 and st["workgroups"] > 5 * simds:
             return f"first_change_kernel<{mode}>, pick_kernel, pick_rest_kernel"
         return f"sweep_kernel<{mode},G={st['waves_per_item']}>"
 
