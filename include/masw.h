@@ -290,9 +290,11 @@ int masw_dispersion_curve_noalloc(masw_ctx *ctx, const double *c_test, int32_t n
                                   uint32_t flags, void *stream, double *C_t,
                                   int32_t *idx, int32_t *status, double *c_ref);
 
-/* Dispersion curves of a batch of models sharing one c grid, in one
- * persistent launch whose work queue hands out (model, wavelength) items
- * longest-expected-first.  Same rules as masw_dispersion_curve. */
+/* Dispersion curves of a batch of models sharing one c grid: persistent
+ * workgroups take (model, wavelength) items from a work queue,
+ * longest-expected-first, in one launch after the staging's, or, on many
+ * wavelengths, in one for the sweep and two for the picks.  Same rules as
+ * masw_dispersion_curve. */
 int masw_dispersion_batch(masw_ctx *ctx, const double *c_test, int32_t n_c,
                           const masw_batch *batch, masw_precision prec,
                           uint32_t flags, void *stream,
@@ -301,12 +303,12 @@ int masw_dispersion_batch(masw_ctx *ctx, const double *c_test, int32_t n_c,
 /* One step of inversion chains (Algorithm 2 over a batch): the batch's
  * curves, as masw_dispersion_batch, and the misfit of every model,
  * misfit[m] = mean over its wavelengths i of |C_t,i - C_e,i| / C_e,i, as
- * masw_misfit computes it (bit for bit), in the same persistent launch: the
- * workgroup that finishes a model's last wavelength reduces the model's
- * misfit.  Batches large enough that the sweep and the picks are launches of
- * their own have a further one for the misfits; their device time
- * (masw_timing) contains it.  C_e: [total wavelengths], laid out as batch->lambda, finite and
- * > 0 (checked on the host for host pointers); misfit: [n_models] (NaN for a
+ * masw_misfit computes it (bit for bit), in the sweep's launch: the workgroup
+ * that finishes a model's last wavelength reduces the model's misfit.  Batches
+ * large enough that the sweep and the picks are launches of their own have a
+ * further one for the misfits; their device time (masw_timing) contains it.
+ * C_e: [total wavelengths], laid out as batch->lambda, finite and > 0 (checked
+ * on the host for host pointers); misfit: [n_models] (NaN for a
  * model without wavelengths, or with a wavelength without a pick).  With
  * MASW_SEARCH_INERTIA the misfit is a second launch after the search, which
  * the device time does not contain.  Same rules as masw_dispersion_batch
@@ -466,8 +468,8 @@ enum {
  * batch (layout as masw_dispersion_batch; idx is typically that call's idx
  * output, or any index whose bracket holds a sign change of a sign map).
  * pick_class[w] = MASW_PICK_*.  c_sec[w] = for MASW_PICK_MODE, the root of F
- * in the bracket (multisection to a bracket no wider than
- * 1e-12 c_test[idx[w]], midpoint), else NaN; c_sec may be NULL.
+ * in the bracket (the first of several; the middle of a bracket no wider than
+ * 1e-12 c_test[idx[w]] around it), else NaN; c_sec may be NULL.
  * c_test: [n_c] as masw_dispersion_curve.  idx, pick_class: int32
  * [lambda_off[n_models]]; c_sec: double [lambda_off[n_models]].  Host
  * pointers are validated (models, wavelengths, grid) and the call is

@@ -142,8 +142,9 @@ __device__ __forceinline__ double root_estimate(double x, double m, int e, int l
 // it 63-fold took 128 for a bracket of the same width, whose middle was 4e5
 // times further from the root: the root estimate is good to about 1e-14.
 // The outcome depends on the eight points alone, so eight lanes of a
-// wavefront (eight wavelengths at once) and a whole wavefront whose lanes
-// repeat them (U: every value uniform) give the same bits.
+// wavefront (eight wavelengths at once) and a whole wavefront that has them in
+// lanes 0..7 (U: every value uniform; the other lanes repeat them, or hold the
+// points between them in refine_and_write's first round) give the same bits.
 constexpr int kMaxRefineRounds = 48;
 
 template <bool U>
@@ -196,6 +197,17 @@ struct Refine8 {
   }
 };
 
+// Whether the signs of 64 points that rise through lanes 0, 8..15, 1, 16..23,
+// 2, ..., 56..63, 7 are those of one change: `differ` has the lanes whose sign
+// differs from the first point's.
+__device__ __forceinline__ bool one_change(unsigned long long differ) {
+  const unsigned long long a = differ & 0xffull, b = differ >> 8;
+  const int f = a ? __ffsll((long long)a) - 1 : 8, t = b ? __ffsll((long long)b) - 1 : 56;
+  // both rise once, and the first of the 56 lies in the eight's interval f - 1
+  return f >= 1 && f < 8 && (a >> f) + 1ull == 1ull << (8 - f) && (b >> t) + 1ull == 1ull << (56 - t) &&
+         t >= 8 * (f - 1) && t <= 8 * f;
+}
+
 // Status, refined root and outputs of the pick at grid index `found`, whose
 // determinant signs are sig_f there and prev_f at found - 1.  Run by one whole
 // wavefront, whose lane 0 stores the outputs.  The first round takes 64 equally
@@ -216,18 +228,6 @@ struct Refine8 {
 // determinant's own at the two grid points, which the first round evaluates,
 // have the last word: kUnconfirmed is added, and nothing written, where they
 // show no change.
-
-// Whether the signs of 64 points that rise through lanes 0, 8..15, 1, 16..23,
-// 2, ..., 56..63, 7 are those of one change: `differ` has the lanes whose sign
-// differs from the first point's.
-__device__ __forceinline__ bool one_change(unsigned long long differ) {
-  const unsigned long long a = differ & 0xffull, b = differ >> 8;
-  const int f = a ? __ffsll((long long)a) - 1 : 8, t = b ? __ffsll((long long)b) - 1 : 56;
-  // both rise once, and the first of the 56 lies in the eight's interval f - 1
-  return f >= 1 && f < 8 && (a >> f) + 1ull == 1ull << (8 - f) && (b >> t) + 1ull == 1ull << (56 - t) &&
-         t >= 8 * (f - 1) && t <= 8 * f;
-}
-
 constexpr unsigned long long kUnconfirmed = 1ull << 63;
 __device__ __forceinline__ unsigned long long refine_and_write(const ItemOut& o, const double* c64, double k64,
                                                                const LayerRec64* L64, int N, int found, int sig_f,

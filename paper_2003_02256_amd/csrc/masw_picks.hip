@@ -31,11 +31,11 @@
 // eliminations at the same points decide.
 // The 1.12 M wavelengths (19,001 velocities): 160 -> 151 ms, split 83 -> 68;
 // before the sweeps' sign function, 211 and 98.  What one launch and three take
-// differs most on short grids: 124,000 wavelengths x 2,000 velocities 2.83 and
-// 2.00 ms (split 2.49 and 1.28), on models of strong contrast, a ninth of whose
-// first candidates are a mode and a pole in one grid step, 2.22 and 1.98 (2.12
-// and 1.90); 46,500 of the latter 0.87 and 0.97 on the split path, the others
-// 0.99 and 0.62.
+// differs most on short grids: 124,000 wavelengths x 2,000 velocities 2.82 and
+// 2.00 ms (split 2.49 and 1.29), on models of strong contrast, a ninth of whose
+// first candidates are a mode and a pole in one grid step, 2.22 and 1.97 (2.11
+// and 1.93); 46,500 of the latter 0.87 and 1.02 on the split path, the others
+// 0.99 and 0.68.
 #define MASW_COEFF_POLICY 1
 #include "masw_inertia_kernel.hpp"
 #include "masw_sweep.hpp"

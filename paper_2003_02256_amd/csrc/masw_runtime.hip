@@ -417,10 +417,11 @@ int run_curves(masw_ctx* ctx, const Inputs& in, masw_precision prec, uint32_t fl
   // Sweep and picks as launches of their own (masw_picks.hip) where there are
   // items enough that their throughput decides, not the deepest of them or the
   // second launch's latency.  One launch against three (ms): 17,281
-  // wavelengths x 9,501 velocities 1.48 and 1.49 (split 1.09 and 1.09), 36,281
-  // 2.78 and 2.67 (1.60 and 1.34), 69,443 5.43 and 5.20 (3.10 and 2.43); x
-  // 19,001 velocities 36,469 5.14 and 5.23 (2.66 and 2.33), 70,340 10.70 and
-  // 10.67 (5.55 and 4.92).  Misfits are then a launch of their own as well.
+  // wavelengths x 9,501 velocities 1.68 and 1.66 (split 1.14 and 1.14), 33,725
+  // 2.90 and 2.89 (1.69 and 1.60), 69,443 5.56 and 5.31 (3.22 and 2.52); x
+  // 19,001 velocities 32,509 4.49 and 4.66 (2.41 and 2.11), 70,340 10.77 and
+  // 10.66 (5.72 and 5.02); x 2,000 35,815 1.06 and 1.06 (0.91 and 0.81), 73,427
+  // 1.96 and 1.62 (1.65 and 1.03).  Misfits are then a launch of their own as well.
   const bool staged = !inertia && G == 1 && ci.n_coop == 0 &&
                       int64_t(in.n_lam) > (mode == 1 ? 32 : 48) * 4 * int64_t(ctx->cus);
 
